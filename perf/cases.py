@@ -1,0 +1,238 @@
+"""Performance cases of the library: what its users have it do, through the public entry points of ``binding`` and
+``sweep``, from single points of a thousand tasksets to batches of a million.
+
+A case names its `kind` (which entry point), a batch size and the generation recipe of its tasksets (the keyword
+arguments of ``taskgen.generate``, flattened to plain values).  Inputs are generated on the device from the seed.
+"""
+import math
+import os
+import sys
+
+import numpy as np
+import torch
+
+_ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if _ROOT not in sys.path:
+    sys.path.insert(0, _ROOT)
+
+from paper_2406_05221_amd import binding as B, sweep, taskgen  # noqa: E402
+
+DEVICE = "cuda:0"
+WAIT = {"busy": B.GCAPS_WAIT_BUSY, "suspend": B.GCAPS_WAIT_SUSPEND}
+POLICY = {"gcaps": B.GCAPS_POLICY_GCAPS, "rr": B.GCAPS_POLICY_RR, "both": B.GCAPS_POLICY_BOTH}
+
+
+def _recipe(cores, per_core, segs, util, eta, share, period, overhead, slice_us):
+    return dict(cores=cores, per_core=per_core, segs=segs, util_lo=util[0], util_hi=util[1], eta_lo=eta[0], eta_hi=eta[1],
+                share_lo=share[0], share_hi=share[1], period_lo=period[0], period_hi=period[1], overhead_lo=overhead[0],
+                overhead_hi=overhead[1], slice_us=slice_us)
+
+
+# the benchmark's workloads (sweep points and grids: their ranges), and its lightly loaded ones
+_W1 = _recipe(2, 3, 1, (0.4, 0.4), (1, 1), (0.10, 0.30), (10_000, 100_000), (200, 200), 1024)
+_W2 = _recipe(4, 4, 3, (0.1, 0.9), (1, 3), (0.10, 0.50), (1_000, 500_000), (200, 200), 1024)
+_W3 = _recipe(4, 5, 3, (0.2, 0.8), (1, 3), (0.10, 0.60), (1_000, 1_000_000), (50, 500), 1024)
+_W4 = _recipe(8, 10, 5, (0.5, 0.9), (1, 5), (0.20, 0.70), (500, 2_000_000), (300, 300), 2048)
+_W5 = _recipe(4, 6, 4, (0.3, 0.9), (1, 4), (0.10, 0.50), (1_000, 1_000_000), (50, 500), 1024)
+_LIGHT = _recipe(4, 5, 3, (0.25, 0.85), (0, 3), (0.05, 0.50), (20_000, 1_000_000), (0, 40), 1024)
+_SIM = _recipe(4, 5, 3, (0.2, 0.4), (1, 3), (0.10, 0.60), (10_000, 100_000), (50, 500), 1024)
+
+
+def listed():
+    def case(name, kind, n_tasksets, recipe, **more):
+        return dict(name=name, kind=kind, n_tasksets=n_tasksets, **recipe, **more)
+
+    return [
+        # one point of a schedulability curve: the smallest call, launches and latency count
+        case("rta_point_1k", "rta", 1_000, _W1, wait="suspend", policy="both", walked=1.0),
+        # a whole utilisation sweep in one batch
+        case("rta_sweep_9k", "rta", 9_000, _W2, wait="busy", policy="both", walked=0.0),
+        # the headline batch: a million mostly overloaded tasksets, settled by their first ranks
+        case("rta_1m", "rta", 1_000_000, _W3, wait="suspend", policy="both", walked=0.0),
+        # a million tasksets of which half are schedulable: long walks through all ranks
+        case("rta_light_1m", "rta", 1_000_000, _LIGHT, wait="suspend", policy="both", walked=0.5),
+        # large systems: 80 tasks on eight cores
+        case("rta_80_tasks_100k", "rta", 100_000, _W4, wait="busy", policy="both", walked=0.0),
+        # a stream of batches generated where they are analysed: one batch of it
+        case("stream_1m", "stream", 1_000_000, _W5, wait="busy", policy="both", walked=0.0),
+        # every task analysed, also below a miss: which tasks of an overloaded system fail
+        case("continue_200k", "continue", 200_000, _W3, wait="suspend", policy="both", walked=1.0),
+        # the search for GPU-segment priorities for the tasksets that fail with equal ones
+        case("gprio_search_1m", "gprio", 1_000_000, _W3, wait="busy", walked=0.0),
+        # bounds for GPU-segment priorities that the caller chose
+        case("gprio_given_200k", "given", 200_000, _W3, wait="suspend", walked=1.0),
+        # one point of the schedulability experiments: tasksets generated on the device, four analyses and two searches
+        # each, grouped by task count
+        dict(name="sweep_point_10k", kind="sweep", n_tasksets=10_000, util=0.4),
+        # observed response times: a second of task time of every taskset under both policies
+        case("simulate_64k", "simulate", 65_536, _SIM, wait="busy", policy="both", horizon=1_000_000),
+        # tasksets and results in host memory: copies in and out around the analysis
+        case("host_200k", "host", 200_000, _W3, wait="suspend", policy="both", walked=0.0),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """Another case of the same ranges: other sizes (odd ones among them), shapes, loads, modes and policies."""
+    kind = rng.choice(["rta", "rta", "rta", "rta", "stream", "continue", "gprio", "given", "sweep", "simulate", "host"])
+    if kind == "sweep":
+        return dict(kind=kind, n_tasksets=_log(rng, 500, 10_000), util=round(rng.uniform(0.1, 0.6), 3))
+    if kind == "rta":
+        cores, per_core = rng.choice([2, 4, 4, 8]), rng.randint(3, 10)
+    else:
+        cores, per_core = rng.choice([2, 3, 4, 4]), rng.randint(3, 6)
+        if cores == 4 and rng.random() < 0.25:
+            per_core = rng.randint(3, 8)
+    n, segs = cores * per_core, rng.randint(1, 5)
+    period_lo = rng.choice([500, 1_000, 10_000, 20_000])
+    period_hi = rng.choice([100_000, 500_000, 1_000_000, 2_000_000])
+    light = rng.random() < 0.4
+    overhead = (0, rng.choice([40, 100])) if light else rng.choice([(200, 200), (50, 500), (300, 300)])
+    util_lo = round(rng.uniform(0.1, 0.5), 3)
+    recipe = _recipe(cores, per_core, segs, (util_lo, round(util_lo + rng.uniform(0.0, 0.4), 3)), (0 if light else 1, segs),
+                     (0.05, 0.50) if light else (0.10, 0.60), (period_lo, period_hi), overhead, rng.choice([512, 1024, 2048]))
+    if kind == "gprio":
+        # loads at which some tasksets pass with equal priorities, some find an assignment and some have none
+        recipe.update(util_lo=round(rng.uniform(0.25, 0.35), 3), util_hi=round(rng.uniform(0.65, 0.85), 3), period_lo=20_000,
+                      period_hi=rng.choice([500_000, 1_000_000, 2_000_000]), overhead_lo=0, overhead_hi=rng.choice([40, 100, 200]))
+    if kind == "simulate":
+        recipe.update(period_lo=10_000, period_hi=100_000, util_lo=0.2, util_hi=0.4)
+        most, least = 65_536 * 20, 1_000
+    elif kind == "rta":
+        most, least = (1_000_000 if n <= 32 else 400_000) * 20, 1_000
+    elif kind in ("stream", "gprio"):
+        most, least = 1_000_000 * 20, 1_000
+    else:
+        most, least = 200_000 * 20, 1_000
+    case = dict(kind=kind, n_tasksets=_log(rng, least, most // n), **recipe, wait=rng.choice(["busy", "suspend"]))
+    if kind == "simulate":
+        case.update(policy=rng.choice(["gcaps", "rr", "both"]), horizon=rng.choice([200_000, 500_000, 1_000_000]))
+    elif kind in ("gprio", "given"):
+        case.update(walked=1.0 if kind == "given" else 0.0)
+    else:
+        case.update(policy=rng.choice(["gcaps", "rr", "both", "both", "both"]), walked=1.0 if kind == "continue" else 0.0)
+    return case
+
+
+class _Context:
+    """A library context on torch's current stream, destroyed with the state that holds it."""
+
+    def __init__(self):
+        self.handle = B.gcaps_create(0, torch.cuda.current_stream().cuda_stream)
+
+    def __del__(self):
+        B.gcaps_destroy(self.handle)
+
+
+def _params(case, seed):
+    return dict(n_cores=case["cores"], tasks_per_core=case["per_core"], max_gseg=case["segs"],
+                util=(case["util_lo"], case["util_hi"]), eta=(case["eta_lo"], case["eta_hi"]),
+                share=(case["share_lo"], case["share_hi"]), period=(case["period_lo"], case["period_hi"]),
+                overhead=(case["overhead_lo"], case["overhead_hi"]), slice_us=case["slice_us"], seed=seed, stream=17)
+
+
+def _empty(*shape, dtype):
+    return torch.empty(shape, dtype=dtype, device=DEVICE)
+
+
+def prepare(case, seed):
+    """What the caller holds before a call: a context, the batch, buffers for the results."""
+    kind, N = case["kind"], case["n_tasksets"]
+    ctx = _Context()
+    state = dict(ctx=ctx, case=case)
+    if kind == "sweep":
+        state["seed"] = seed
+        return state
+    params = _params(case, seed)
+    n, P = case["cores"] * case["per_core"], B.npol(POLICY[case.get("policy", "gcaps")])
+    if kind == "host":
+        state["batch"] = taskgen.generate(N, **params)
+        return state
+    batch = B.gcaps_taskgen_device(ctx.handle, N, **params)
+    state["batch"] = batch
+    if kind == "stream":
+        state["params"] = params
+    if kind == "continue":
+        B.gcaps_set_continue_after_miss(ctx.handle, True)
+    if kind == "simulate":
+        state.update(mort=_empty(P, N, n, dtype=torch.int64), jobs=_empty(P, N, n, dtype=torch.int32),
+                     flag=_empty(P, N, dtype=torch.uint8))
+    elif kind in ("gprio", "given"):
+        state.update(gprio=_empty(N, n, dtype=torch.int32), resp=_empty(N, n, dtype=torch.int64),
+                     sched=_empty(N, dtype=torch.uint8))
+        if kind == "gprio":
+            # the tasksets that pass with equal priorities are not searched
+            resp, sched = _empty(1, N, n, dtype=torch.int64), _empty(1, N, dtype=torch.uint8)
+            B.gcaps_rta_batch_device(ctx.handle, batch, B.GCAPS_POLICY_GCAPS, WAIT[case["wait"]], resp, sched)
+            state["skip"] = sched[0].clone()
+        else:
+            # an order of the caller's own across cores that agrees with the CPU order on every core
+            g = torch.Generator(device=DEVICE).manual_seed(seed)
+            shift = torch.randint(0, n, (N, case["cores"]), generator=g, device=DEVICE, dtype=torch.int64)
+            state["gprio"] = (batch["prio"] + torch.gather(shift, 1, batch["core"].long())).to(torch.int32).contiguous()
+    else:
+        state.update(resp=_empty(P, N, n, dtype=torch.int64), sched=_empty(P, N, dtype=torch.uint8))
+    torch.cuda.synchronize()
+    return state
+
+
+def run(state):
+    """One call."""
+    case, ctx = state["case"], state["ctx"].handle
+    kind = case["kind"]
+    if kind == "sweep":
+        util = (case["util"], case["util"])
+        groups = B.gcaps_table3_device(ctx, case["n_tasksets"], seed=state["seed"], stream=300, util=util)
+        return sweep.verdicts_device(ctx, groups, case["n_tasksets"])
+    wait = WAIT[case["wait"]]
+    if kind == "host":
+        return B.gcaps_rta_batch(ctx, state["batch"], POLICY[case["policy"]], wait)
+    batch = state["batch"]
+    if kind == "simulate":
+        B.gcaps_simulate_batch_device(ctx, batch, POLICY[case["policy"]], wait, case["horizon"], state["mort"],
+                                      state["jobs"], state["flag"])
+        return state["mort"], state["jobs"], state["flag"]
+    if kind == "gprio":
+        B.gcaps_gprio_assign_batch_device(ctx, batch, wait, state["skip"], state["gprio"], state["resp"], state["sched"])
+        return state["gprio"], state["resp"], state["sched"]
+    if kind == "given":
+        B.gcaps_gprio_rta_batch_device(ctx, batch, wait, state["gprio"], state["resp"], state["sched"])
+        return state["resp"], state["sched"]
+    if kind == "stream":
+        B.gcaps_taskgen_device(ctx, case["n_tasksets"], out=batch, **state["params"])
+    B.gcaps_rta_batch_device(ctx, batch, POLICY[case["policy"]], wait, state["resp"], state["sched"])
+    if kind == "stream":
+        return dict(batch, resp=state["resp"], sched=state["sched"])
+    return state["resp"], state["sched"]
+
+
+def work(case):
+    """Bytes: every input and every output once.  Operations: six per interference term (add, three for the ceil of a
+    quotient, multiply-add, compare) of one evaluation per task and policy in the tasksets that are walked to the end;
+    simulation: 6 n + 40 per event, a job having a release, its CPU and GPU segments and their updates as events."""
+    N = case["n_tasksets"]
+    if case["kind"] == "sweep":
+        n, S = 18, 3  # mean task count of the recipe
+        return {"bytes": N * (6 + 2 * (12 + 18 * n + 8 * n * S)), "flops": N * 6 * 4 * n * (n - 1) / 2}
+    n, S = case["cores"] * case["per_core"], case["segs"]
+    inputs = 12 + 18 * n + 8 * n * S
+    if case["kind"] == "simulate":
+        P = B.npol(POLICY[case["policy"]])
+        lo, hi = case["period_lo"], case["period_hi"]
+        jobs = n * case["horizon"] * (1.0 / lo - 1.0 / hi) / math.log(hi / lo)
+        events = jobs * (2 + 2 * (case["eta_lo"] + case["eta_hi"]))
+        return {"bytes": N * (inputs - 4 * n + P * (12 * n + 1)), "flops": N * P * events * (6 * n + 40)}
+    if case["kind"] in ("gprio", "given"):
+        return {"bytes": N * (inputs - 8 + 12 * n + 1 + (1 if case["kind"] == "gprio" else 0)),
+                "flops": N * case["walked"] * 6 * n * (n - 1) / 2}
+    P = B.npol(POLICY[case["policy"]])
+    moved = inputs + P * (8 * n + 1) + (inputs if case["kind"] == "stream" else 0)
+    return {"bytes": N * moved, "flops": N * P * case["walked"] * 6 * n * (n - 1) / 2}
+
+
+def tolerance(case):
+    """Integer results: the same on every route."""
+    return "exact"
