@@ -5,17 +5,10 @@ A case names its `kind` (which entry point), a batch size and the generation rec
 arguments of ``taskgen.generate``, flattened to plain values).  Inputs are generated on the device from the seed.
 """
 import math
-import os
-import sys
 
-import numpy as np
 import torch
 
-_ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-if _ROOT not in sys.path:
-    sys.path.insert(0, _ROOT)
-
-from paper_2406_05221_amd import binding as B, sweep, taskgen  # noqa: E402
+from paper_2406_05221_amd import binding as B, sweep, taskgen
 
 DEVICE = "cuda:0"
 WAIT = {"busy": B.GCAPS_WAIT_BUSY, "suspend": B.GCAPS_WAIT_SUSPEND}
