@@ -142,3 +142,19 @@ def test_sweep_with_best_effort_tasks_matches_the_oracle(oracle, gpu):
     # (their GPU segments still take their time slices)
     gain = {c: rows[1][1][c] - rows[0][1][c] for c in sweep.COLUMNS}
     assert gain["gcaps_suspend"] > 0 and gain["gcaps_busy"] > 0
+
+
+@pytest.mark.parametrize("N,overrides", [(8_191, dict(tasks_per_cpu=(4, 4))), (8_193, dict(tasks_per_cpu=(4, 4))), (20_481, dict(tasks_per_cpu=(4, 4))),
+                                         (33, dict(n_cpus=1, tasks_per_cpu=(1, 1))), (70, dict(n_cpus=8, tasks_per_cpu=(8, 8), eta=(1, 5))),
+                                         (1, dict(n_cpus=3, tasks_per_cpu=(5, 5), period=(1 << 24, 1 << 25)))])
+def test_table3_generation_at_the_edges_of_its_tiles(gpu, N, overrides):
+    """Tiles of 4, 8 and 16 tasksets per wavefront (up to 8,192 and up to 20,480 tasksets, and beyond), remainders, one task and 64 tasks, periods on both sides of the packed (period, task) keys: the host generator's batch."""
+    from paper_2406_05221_amd import taskgen
+    B, ctx, _ = gpu
+    host = taskgen.table3(N, seed=5, stream=302, **overrides)
+    dev = B.gcaps_table3_device(ctx, N, seed=5, stream=302, **overrides)
+    assert sorted(dev) == sorted(host)
+    for n in host:
+        got = B.to_host(dev[n][1])
+        for name in host[n][1]:
+            assert np.array_equal(got[name], host[n][1][name]), (n, name)
