@@ -737,41 +737,70 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
   });
 }
 
+/* the longest schedules first; null (caller order) where the list cannot be had: no memory, or the stream is recording
+ * and no earlier call has made room for it */
+const u32 *simulation_order(gcaps_ctx *ctx, const gcaps_batch *sub, u32 horizon) {
+  const u32 N = sub->n_tasksets, blocks = (N + 255u) / 256u;
+  if (ctx->pool.deep_sorted.reserve((size_t)N * sizeof(u32), !ctx->capturing) != GCAPS_OK ||
+      ctx->pool.deep_aux.reserve((size_t)N * 2 * sizeof(u32), !ctx->capturing) != GCAPS_OK)
+    return nullptr;
+  u32 *order = (u32 *)ctx->pool.deep_sorted.ptr, *bucket = (u32 *)ctx->pool.deep_aux.ptr, *position = bucket + N;
+  u32 *hist = status_of(ctx) + fast::ST_ORDER_HIST;
+  hipLaunchKernelGGL(sim::order_count_kernel, dim3(blocks), dim3(256), 0, ctx->stream, *sub, (float)horizon, hist,
+                     bucket, position);
+  hipLaunchKernelGGL(sim::order_kernel, dim3(blocks), dim3(256), 0, ctx->stream, N, (const u32 *)hist,
+                     (const u32 *)bucket, (const u32 *)position, order);
+  return order;
+}
+
+/* one launch for all planes: as many workgroups of W lanes per plane as are resident at once; their lanes take further
+ * tasksets as they finish.  The launch prepares the status words of the next call. */
+template <bool BUSY, int W>
+int launch_simulate(gcaps_ctx *ctx, const gcaps_batch *sub, const u32 *offset, const int *gprio, const u32 *order,
+                    int policy, u32 horizon, long long *mort, u32 *jobs, uint8_t *flag, size_t task_stride, size_t ts_stride) {
+  auto fn = sim::simulate_kernel<BUSY, W>;
+  const size_t lds = sim::lds_bytes(sub->n_tasks, W);
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, W, lds) != hipSuccess || per_cu < 1) {
+    (void)hipGetLastError();
+    per_cu = 1;
+  }
+  u32 blocks = (u32)ctx->n_cu * (u32)per_cu;
+  const u32 tiles = (sub->n_tasksets + (u32)W - 1u) / (u32)W;
+  if (blocks > tiles) blocks = tiles;
+  if (ctx->sim_blocks_cap && blocks > ctx->sim_blocks_cap) blocks = ctx->sim_blocks_cap;
+  hipLaunchKernelGGL(fn, dim3(blocks, policy == GCAPS_POLICY_BOTH ? 2u : 1u), dim3(W), lds, ctx->stream, *sub, offset,
+                     gprio, order, policy, horizon, mort, jobs, flag, task_stride, ts_stride, status_of(ctx), ctx->ts_offset,
+                     ctx->next_status, (u32)fast::kStatusWords);
+  return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
+}
+
 /* Schedule simulation (Sec. 6.2: observed response times) of every taskset, one lane each */
 int run_simulate(gcaps_ctx *ctx, const gcaps_batch *b, const uint32_t *d_offset, const int32_t *d_gprio, int policy,
                  int wait_mode,
                  uint32_t horizon, int64_t *d_mort, uint32_t *d_jobs, uint8_t *d_flag) {
   const u64 n = b->n_tasks, N = b->n_tasksets;
-  const size_t lds = sim::lds_bytes(b->n_tasks);
-  if (lds > (size_t)ctx->lds_limit) return GCAPS_EINVAL;
-  const u32 planes = policy == GCAPS_POLICY_BOTH ? 2u : 1u;
   return for_chunks(ctx, b, [&](const gcaps_batch *sub, u64 c0) {
     if (begin_chunk(ctx, c0 == 0) != GCAPS_OK) return (int)GCAPS_EDEVICE;
     ctx->wide_only = true;
-    /* one launch per policy plane, as many single-wavefront workgroups as are resident at once; their lanes take
-     * further tasksets as they finish.  The last launch prepares the status words of the next call. */
-    const bool busy = wait_mode == GCAPS_WAIT_BUSY;
-    for (u32 plane = 0; plane < planes; ++plane) {
-      const bool gc = (policy == GCAPS_POLICY_BOTH ? (int)plane + 1 : policy) == GCAPS_POLICY_GCAPS;
-      auto fn = gc ? (busy ? sim::simulate_kernel<true, true> : sim::simulate_kernel<true, false>)
-                   : (busy ? sim::simulate_kernel<false, true> : sim::simulate_kernel<false, false>);
-      int per_cu = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, 64, lds) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        per_cu = 1;
-      }
-      u32 blocks = (u32)ctx->n_cu * (u32)per_cu;
-      const u32 tiles = (sub->n_tasksets + 63u) / 64u;
-      if (blocks > tiles) blocks = tiles;
-      if (ctx->sim_blocks_cap && blocks > ctx->sim_blocks_cap) blocks = ctx->sim_blocks_cap;
-      hipLaunchKernelGGL(fn, dim3(blocks), dim3(64), lds, ctx->stream, *sub, d_offset ? d_offset + c0 * n : nullptr,
-                         d_gprio ? (const int *)(d_gprio + c0 * n) : nullptr, plane, horizon,
-                         (long long *)(d_mort + c0 * n), d_jobs + c0 * n, d_flag + c0, (size_t)(N * n), (size_t)N,
-                         status_of(ctx), ctx->ts_offset, plane + 1 == planes ? ctx->next_status : nullptr,
-                         (u32)fast::kStatusWords);
-      if (hipGetLastError() != hipSuccess) return (int)GCAPS_EDEVICE;
-    }
-    return (int)GCAPS_OK;
+    const u32 *order = simulation_order(ctx, sub, horizon);
+    auto go = [&](auto busy, auto lanes) {
+      return launch_simulate<decltype(busy)::value, decltype(lanes)::value>(
+          ctx, sub, d_offset ? d_offset + c0 * n : nullptr, d_gprio ? (const int *)(d_gprio + c0 * n) : nullptr, order,
+          policy, horizon, (long long *)(d_mort + c0 * n), d_jobs + c0 * n, d_flag + c0, (size_t)(N * n), (size_t)N);
+    };
+    auto with = [&](auto lanes) {
+      return wait_mode == GCAPS_WAIT_BUSY ? go(std::true_type{}, lanes) : go(std::false_type{}, lanes);
+    };
+    /* Lanes per wavefront: few while that leaves at most 16 wavefronts per CU, for a step takes the longer the more
+     * lanes take part; full half-wavefronts beyond, where the chip is busy.  20 tasks, both policies, 4 / 8 / 16 / 32
+     * lanes: 1,000 tasksets 23 / 25 / 30 / 35 ms, 8,192 23 / 31 / 35 / 37, 16,384 34 / 27 / 33 / 40, 65,536
+     * 97 / 66 / 48 / 45 (64 lanes: 49, the columns of fewer wavefronts fit the LDS). */
+    const u64 schedules = (u64)sub->n_tasksets * (policy == GCAPS_POLICY_BOTH ? 2u : 1u), most = (u64)ctx->n_cu * 16u;
+    if (schedules <= 4u * most) return with(std::integral_constant<int, 4>{});
+    if (schedules <= 8u * most) return with(std::integral_constant<int, 8>{});
+    if (schedules <= 16u * most) return with(std::integral_constant<int, 16>{});
+    return with(std::integral_constant<int, 32>{});
   });
 }
 

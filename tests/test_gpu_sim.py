@@ -252,6 +252,27 @@ def test_lanes_take_further_tasksets(oracle, monkeypatch):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("N,cores,per_core,horizon", [(1, 1, 1, 3000), (3, 8, 4, 2000), (1031, 6, 5, 900),
+                                                      (8193, 5, 3, 300), (20_001, 2, 2, 300), (70_003, 1, 3, 200)])
+def test_lane_counts_and_core_counts(oracle, gpu, N, cores, per_core, horizon):
+    """Every number of lanes per wavefront (by the size of the call), up to and beyond the four cores whose tasks are
+    held in registers, task counts that are no multiple of four, the last lane of the last wavefront; ties in the
+    GPU-segment priorities."""
+    from paper_2406_05221_amd import taskgen
+    B, ctx, _ = gpu
+    batch = taskgen.generate(N, n_cores=cores, tasks_per_core=per_core, max_gseg=2, util=(0.2, 0.6), eta=(0, 2),
+                             share=(0.1, 0.5), period=(40, 400), overhead=(1, 3), slice_us=8, seed=N, stream=51)
+    n = cores * per_core
+    gprio = np.random.default_rng(N).integers(0, max(2, n // 2), (N, n)).astype(np.int32)
+    rows = np.unique(np.linspace(0, N - 1, 400).astype(int))
+    sample = {k: v[rows] for k, v in batch.items()}
+    for wait in (BUSY, SUSPEND):
+        for gp in (None, gprio):
+            got = B.gcaps_simulate_batch(ctx, batch, BOTH, wait, horizon, gprio=gp)
+            want = oracle.simulate_batch(sample, BOTH, wait, horizon, gprio=None if gp is None else gp[rows], threads=16)
+            assert all((g[:, rows] == w).all() for g, w in zip(got, want))
+
+
 def test_captured_simulation_replays(oracle, monkeypatch):
     """The device entry point recorded into a HIP graph (after a warm-up call that made the context's allocations)
     and replayed, with eager calls between the replays; few workgroups, so that the hand-out counters are part of
