@@ -79,6 +79,28 @@ def test_shapes_and_ragged_batches(oracle, gpu, shape):
         compare(oracle, B, ctx, batch)
 
 
+@pytest.mark.parametrize("n_cores,per_core,S", [(4, 5, 3), (3, 8, 4), (2, 16, 5)])
+@pytest.mark.parametrize("period", [(257, 259), (510, 514), (65_535, 65_538), (2**21 - 3, 2**21)])
+def test_job_counts_at_the_edges_of_a_period(oracle, gpu, period, n_cores, per_core, S):
+    """Response times that end on and one beside a multiple of a period, at the ends of the range of periods and around
+    powers of two, where the reciprocals round differently.  Exact integers: no tolerance."""
+    B, ctx, _ = gpu
+    rng = np.random.default_rng(period[0] + S)
+    batch = relaxed_workload(2_000, seed=41, n_cores=n_cores, per_core=per_core, S=S)
+    n = batch["cpu_us"].shape[1]
+    T = rng.integers(period[0], period[1] + 1, batch["period_us"].shape).astype(np.uint32)
+    batch["period_us"] = batch["deadline_us"] = T
+    # demands near simple fractions of a period, so that sums meet multiples of it and miss them by one
+    part = rng.choice([n, 2 * n, 4 * n, 8 * n, 16 * n], size=T.shape)
+    batch["cpu_us"] = np.maximum(1, T // part + rng.integers(-1, 2, T.shape)).astype(np.uint32)
+    for key in ("gm_us", "ge_us"):
+        batch[key] = np.minimum(batch[key], (T // (8 * n))[:, :, None]).astype(np.uint32)
+    batch["eps_us"] = rng.integers(0, 2, batch["eps_us"].shape).astype(np.uint32)
+    batch["theta_us"] = rng.integers(0, 2, batch["theta_us"].shape).astype(np.uint32)
+    compare(oracle, B, ctx, batch)
+    compare_continue(oracle, B, batch)
+
+
 def test_priority_ties_and_cpu_only_tasks(oracle, gpu):
     B, ctx, _ = gpu
     rng = np.random.default_rng(5)
