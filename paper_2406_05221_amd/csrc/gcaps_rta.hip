@@ -348,14 +348,14 @@ int launch_deep_q(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_r
 }
 
 /* second launch in its register form (rta_quad.hip.inc): four lanes per taskset, n <= 4 * NSMAX */
-template <bool BUSY, int NSMAX, int SEGS>
+template <bool BUSY, int NSMAX, int SEGS, bool ALL>
 int launch_quad(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_resp, uint8_t *d_sched, u32 kr,
                 const fast::ListSpec &dl) {
   const u32 n = b->n_tasks, N = b->n_tasksets;
   const size_t lds = fast::quad_lds_bytes(n);
   /* exactly as many workgroups as are resident at once: a workgroup's first tile is its own index */
   int per_cu = 0;
-  const void *fn = (const void *)fast::rta_quad_kernel<BUSY, NSMAX, SEGS>;
+  const void *fn = (const void *)fast::rta_quad_kernel<BUSY, NSMAX, SEGS, ALL>;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64, lds) != hipSuccess || per_cu < 1) {
     (void)hipGetLastError();
     per_cu = 1;
@@ -363,9 +363,9 @@ int launch_quad(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_res
   u32 blocks = (u32)ctx->n_cu * (u32)per_cu;
   const u32 max_tiles = (N + 15u) / 16u + fast::kListRegions;
   if (blocks > max_tiles) blocks = max_tiles;
-  hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS>), dim3(blocks), dim3(64), lds, ctx->stream, *b, policy,
-                     (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
-                     ctx->resp_stride, ctx->sched_stride);
+  hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, ALL>), dim3(blocks), dim3(64), lds, ctx->stream, *b,
+                     policy, (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
+                     ctx->resp_stride, ctx->sched_stride, ctx->ts_offset, ctx->cont != 0);
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -373,8 +373,8 @@ int launch_quad_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_m
                     uint8_t *d_sched, u32 kr, const fast::ListSpec &dl) {
   const bool busy = wait_mode == GCAPS_WAIT_BUSY;
 #define GCAPS_QUAD_S(NS, SEGS)                                                  \
-  (busy ? launch_quad<true, NS, SEGS>(ctx, b, policy, d_resp, d_sched, kr, dl) \
-        : launch_quad<false, NS, SEGS>(ctx, b, policy, d_resp, d_sched, kr, dl))
+  (busy ? launch_quad<true, NS, SEGS, false>(ctx, b, policy, d_resp, d_sched, kr, dl) \
+        : launch_quad<false, NS, SEGS, false>(ctx, b, policy, d_resp, d_sched, kr, dl))
 #define GCAPS_QUAD(NS)                                                                           \
   (b->max_gseg <= 3 ? GCAPS_QUAD_S(NS, 3)                                                        \
    : b->max_gseg <= 4 ? GCAPS_QUAD_S(NS, 4)                                                      \
@@ -385,6 +385,27 @@ int launch_quad_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_m
   return GCAPS_QUAD(8);
 #undef GCAPS_QUAD
 #undef GCAPS_QUAD_S
+}
+
+/* The register form over every taskset of the chunk, S <= kPrefetchSegs.  Continue-after-miss, 200,000 tasksets of
+ * 20 tasks x 3 segments, both policies, self-suspension: 201 us, with term records in LDS (rta_deep_kernel) 426. */
+int launch_quad_all(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp, uint8_t *d_sched) {
+  const bool busy = wait_mode == GCAPS_WAIT_BUSY;
+  const fast::ListSpec dl{nullptr, nullptr, 1u, b->n_tasksets, nullptr, nullptr, nullptr};
+#define GCAPS_QUAD_S(NS, SEGS)                                                \
+  (busy ? launch_quad<true, NS, SEGS, true>(ctx, b, policy, d_resp, d_sched, 0u, dl) \
+        : launch_quad<false, NS, SEGS, true>(ctx, b, policy, d_resp, d_sched, 0u, dl))
+#define GCAPS_QUAD(NS) (b->max_gseg <= 3 ? GCAPS_QUAD_S(NS, 3) : GCAPS_QUAD_S(NS, fast::kPrefetchSegs))
+  if (b->n_tasks <= 20) return GCAPS_QUAD(5);
+  if (b->n_tasks <= 24) return GCAPS_QUAD(6);
+  return GCAPS_QUAD(8);
+#undef GCAPS_QUAD
+#undef GCAPS_QUAD_S
+}
+
+bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
+  return ctx->deep_lanes == 4 && b->n_tasks <= fast::kQuadMaxTasks && b->max_gseg <= (u32)fast::kPrefetchSegs &&
+         !ctx->legacy_deep;
 }
 
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
@@ -440,7 +461,8 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
 
   if (ctx->cont) {
     /* continue-after-miss: nothing is settled early, the full-depth launch takes every taskset */
-    rc = launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
+    rc = quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
+                                  : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
     if (rc != GCAPS_OK) return rc;
     const u32 *count = (const u32 *)status_of(ctx) + fast::ST_WIDE_COUNT;
     return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, (const u32 *)ctx->pool.wide_list.ptr, count,
@@ -949,14 +971,15 @@ extern "C" int gcaps_create(gcaps_ctx **out, int device_id, void *hip_stream) {
         (const void *)fast::rta_deep_kernel<true, 8, false>, (const void *)fast::rta_deep_kernel<false, 8, false>,
         (const void *)fast::rta_deep_kernel<true, 4, true>, (const void *)fast::rta_deep_kernel<false, 4, true>,
         (const void *)fast::rta_deep_kernel<true, 8, true>, (const void *)fast::rta_deep_kernel<false, 8, true>,
-#define GCAPS_QUAD_KERNELS(NS)                                                                                        \
-  (const void *)fast::rta_quad_kernel<true, NS, 3>, (const void *)fast::rta_quad_kernel<false, NS, 3>,                \
-      (const void *)fast::rta_quad_kernel<true, NS, 4>, (const void *)fast::rta_quad_kernel<false, NS, 4>,            \
-      (const void *)fast::rta_quad_kernel<true, NS, fast::kPrefetchSegs>,                                             \
-      (const void *)fast::rta_quad_kernel<false, NS, fast::kPrefetchSegs>,                                            \
-      (const void *)fast::rta_quad_kernel<true, NS, 0>, (const void *)fast::rta_quad_kernel<false, NS, 0>
+#define GCAPS_QUAD_KERNEL(NS, SEGS, ALL)                                                                          \
+  (const void *)fast::rta_quad_kernel<true, NS, SEGS, ALL>, (const void *)fast::rta_quad_kernel<false, NS, SEGS, ALL>
+#define GCAPS_QUAD_KERNELS(NS)                                                                                      \
+  GCAPS_QUAD_KERNEL(NS, 3, false), GCAPS_QUAD_KERNEL(NS, 4, false), GCAPS_QUAD_KERNEL(NS, fast::kPrefetchSegs, false), \
+      GCAPS_QUAD_KERNEL(NS, 0, false), GCAPS_QUAD_KERNEL(NS, 3, true),                                              \
+      GCAPS_QUAD_KERNEL(NS, fast::kPrefetchSegs, true)
         GCAPS_QUAD_KERNELS(5), GCAPS_QUAD_KERNELS(6), GCAPS_QUAD_KERNELS(8)};
 #undef GCAPS_QUAD_KERNELS
+#undef GCAPS_QUAD_KERNEL
     bool raised = want > 65536;
     for (size_t k = 0; k < sizeof(kernels) / sizeof(kernels[0]) && raised; ++k)
       raised = hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize, (int)want) == hipSuccess;
