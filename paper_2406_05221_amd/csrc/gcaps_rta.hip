@@ -137,6 +137,7 @@ struct gcaps_ctx {
   u32 sim_blocks_cap = 0;   /* GCAPS_SIM_BLOCKS: fewer workgroups per simulation launch than fit the GPU (testing:
                                every lane then takes many tasksets) */
   u32 screen_tasks = 4;     /* tasks per taskset analysed by the first fast launch (GCAPS_SCREEN_TASKS) */
+  int one_launch = -1;      /* GCAPS_ONE_LAUNCH: calls of at most this many tasksets take one launch (-1: by the rule) */
   u32 deep_lanes = 4;       /* lanes per taskset in the second fast launch, 4 or 8 (GCAPS_DEEP_LANES) */
   bool gen_by_taskset = false; /* GCAPS_GEN_KERNEL=taskset: the generator with one lane per taskset */
   bool gprio_list = false;  /* GCAPS_GPRIO_KERNEL=list: the priority search as two launches with a list between them */
@@ -408,6 +409,22 @@ bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
          !ctx->legacy_deep;
 }
 
+/* One full-depth launch for the whole call instead of two with a list between them.  A small call is bound by latency:
+ * the chain of dependent loads of a launch, and a second launch behind it; a large one by work, most of which the first
+ * launch of the two saves where most tasksets miss within their first ranks.  The line lies where the elements of the
+ * call fill the chip twice over.  us in two launches / in one, both policies, self-suspension:
+ *   6 tasks x 1 segment, 1,000 tasksets: 27.5 / 16.0;  16 x 3, 9,000: 33.9 / 23.5, 30,000: 40.0 / 32.4, 65,536: 44.3 / 46.0;
+ *   20 x 3, 1,000 / 16,000 / 65,536: 37.1 / 25.3, 53.3 / 41.9, 60.8 / 63.8; lightly loaded 58.5 / 42.6, 67.5 / 49.4, 109.6 / 86.1;
+ *   24 x 4 settled by the first ranks, 1,000 / 16,384 / 32,768: 20.8 / 19.5, 29.7 / 26.2, 32.2 / 33.9.
+ * Beyond 24 tasks one launch gives less on lightly loaded tasksets (28 x 3, 1,000: 83.7 / 65.8) and loses more on
+ * overloaded ones (32 x 5, 1,000 / 16,384: 23.2 / 27.8, 27.0 / 37.7: seven or eight rounds of elements to stage). */
+bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
+  if (ctx->binning || ctx->screen_tasks != 4u || !quad_all_applies(ctx, b)) return false;
+  if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
+  return b->n_tasks <= 24u && b->n_tasksets <= (u32)ctx->n_cu * 128u &&
+         (u64)b->n_tasksets * b->n_tasks <= (u64)ctx->n_cu * 2048u;
+}
+
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
   return !ctx->cont && ctx->deep_lanes == 4 && b->n_tasks <= fast::kQuadMaxTasks && !ctx->legacy_deep && kr <= 4u;
 }
@@ -459,7 +476,7 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
     rc = ctx->pool.deep_aux.reserve((size_t)ctx->region_cap * fast::kListRegions * 2 * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
 
-  if (ctx->cont) {
+  if (ctx->cont || one_launch_applies(ctx, b)) {
     /* continue-after-miss: nothing is settled early, the full-depth launch takes every taskset */
     rc = quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
                                   : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
@@ -918,6 +935,10 @@ extern "C" int gcaps_create(gcaps_ctx **out, int device_id, void *hip_stream) {
   if (const char *e = getenv("GCAPS_SCREEN_TASKS")) {
     const long v = strtol(e, nullptr, 10);
     if (v >= 1 && v <= 255) ctx->screen_tasks = (u32)v;
+  }
+  if (const char *e = getenv("GCAPS_ONE_LAUNCH")) {
+    const long v = strtol(e, nullptr, 10);
+    if (v >= 0 && v <= 0x7fffffff) ctx->one_launch = (int)v;
   }
   if (const char *e = getenv("GCAPS_DEEP_KERNEL")) ctx->legacy_deep = e[0] == 'l';
   if (const char *e = getenv("GCAPS_GPRIO_KERNEL")) ctx->gprio_list = e[0] == 'l';

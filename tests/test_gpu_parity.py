@@ -277,6 +277,38 @@ def test_launch_split_knobs(oracle, monkeypatch, screen_tasks, deep_lanes, deep_
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("tasksets", [0, 100_000])
+@pytest.mark.parametrize("shape", [(1, 1, 0), (2, 3, 8), (4, 5, 3), (4, 6, 4), (5, 5, 5), (4, 8, 1), (4, 8, 9)])
+def test_calls_in_one_launch_and_in_two(oracle, monkeypatch, shape, tasksets):
+    """Small calls of small shapes take one full-depth launch, others two launches with a list between them: both
+    routes for every shape (one launch: up to 32 tasks and eight segments), against the oracle."""
+    import torch
+    from paper_2406_05221_amd import binding as B, taskgen
+    monkeypatch.setenv("GCAPS_ONE_LAUNCH", str(tasksets))
+    cores, per_core, S = shape
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        for policy in (GCAPS, RR, BOTH):
+            compare(oracle, B, ctx, relaxed_workload(1_003, seed=51, n_cores=cores, per_core=per_core, S=S), policy)
+        batch = relaxed_workload(1_003, seed=52, n_cores=cores, per_core=per_core, S=S)
+        # misses early in the walk, tasks outside the 24-bit range, equal priorities
+        rng = np.random.default_rng(52)
+        batch["deadline_us"] = np.where(rng.random(batch["deadline_us"].shape) < 0.1, batch["deadline_us"] // 30 + 1,
+                                        batch["deadline_us"]).astype(np.uint32)
+        batch["cpu_us"] = np.where(rng.random(batch["cpu_us"].shape) < 0.01, 2**31, batch["cpu_us"]).astype(np.uint32)
+        batch["prio"] = rng.integers(-3, 4, batch["prio"].shape).astype(np.int32)
+        compare(oracle, B, ctx, batch)
+        bad = {k: v.copy() for k, v in batch.items()}
+        bad["period_us"][137, 0] = 0
+        bad["slice_us"][700] = 0
+        with pytest.raises(B.GcapsError) as e:
+            B.gcaps_rta_batch(ctx, bad, BOTH, BUSY)
+        assert e.value.code == B.GCAPS_ETASK and e.value.first_bad == 137
+        compare(oracle, B, ctx, batch)
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_out_of_range_values_below_the_screened_ranks(oracle, gpu):
     """Values outside the fast kernels' range in LOW-priority tasks only: the first launch does not
     look at them, the second hands the taskset over to the 64-bit kernel when it gets there."""
