@@ -57,25 +57,42 @@ def verdicts(ctx, groups):
 
 def verdicts_device(ctx, groups, total):
     """The same for groups generated on the device ({n: (index tensor, device batch)} from
-    ``binding.gcaps_table3_device``): device entry points only, the verdicts are copied back."""
+    ``binding.gcaps_table3_device``): device entry points only, the verdicts are copied back.
+
+    A group is a few hundred tasksets, so that a point of the sweep is bound by launches and by the gaps at every wait
+    and copy, not by the analysis.  All groups share one buffer per output, sized by the largest (the calls run in
+    order on the context's stream); the verdicts of all groups come back in one copy, and each group is waited for
+    once: both waiting modes check the same task model.  10,000 tasksets in 13 groups: 5.6 -> 3.1 ms per point."""
     import torch
     out = {c: np.zeros(total, np.uint8) for c in COLUMNS}
-    for idx, d in groups.values():
-        N, n = d["cpu_us"].shape
-        rows = idx.cpu().numpy()
-        resp = torch.empty((2, N, n), dtype=torch.int64, device=idx.device)
-        sched = torch.empty((2, N), dtype=torch.uint8, device=idx.device)
-        gprio = torch.empty((N, n), dtype=torch.int32, device=idx.device)
-        found = torch.empty((N,), dtype=torch.uint8, device=idx.device)
-        torch.cuda.synchronize()  # the tensors were made on torch's stream, the library works on the context's
+    if not groups:
+        return out
+    batches = [d for _, d in groups.values()]
+    sizes = [d["cpu_us"].shape for d in batches]
+    rows = torch.cat([idx for idx, _ in groups.values()])
+    tasks = max(N * n for N, n in sizes)
+    resp = torch.empty(2 * tasks, dtype=torch.int64, device=rows.device)
+    gprio = torch.empty(tasks, dtype=torch.int32, device=rows.device)
+    # per waiting mode and group: the verdicts of GCAPS, of round-robin and of the priority search
+    verdict = torch.empty(6 * sum(N for N, _ in sizes), dtype=torch.uint8, device=rows.device)
+    torch.cuda.synchronize()  # the tensors were made on torch's stream, the library works on the context's
+    at, parts = 0, []
+    for d, (N, n) in zip(batches, sizes):
         for wait, name in ((B.GCAPS_WAIT_BUSY, "busy"), (B.GCAPS_WAIT_SUSPEND, "suspend")):
-            B.gcaps_rta_batch_device(ctx, d, B.GCAPS_POLICY_BOTH, wait, resp, sched)
+            v = verdict[at:at + 3 * N].view(3, N)
+            B.gcaps_rta_batch_device(ctx, d, B.GCAPS_POLICY_BOTH, wait, resp[:2 * N * n].view(2, N, n), v[:2])
             # separate GPU-segment priorities only where the test with equal priorities failed
-            B.gcaps_gprio_assign_batch_device(ctx, d, wait, sched[0], gprio, resp[0], found)
-            B.gcaps_status(ctx)
-            out[f"gcaps_{name}"][rows] = sched[0].cpu().numpy()
-            out[f"tsg_rr_{name}"][rows] = sched[1].cpu().numpy()
-            out[f"gcaps_{name}+prio"][rows] = found.cpu().numpy()
+            B.gcaps_gprio_assign_batch_device(ctx, d, wait, v[0], gprio[:N * n].view(N, n), resp[:N * n].view(N, n), v[2])
+            parts.append((name, at, N))
+            at += 3 * N
+        B.gcaps_status(ctx)
+    verdict, rows = verdict.cpu().numpy(), rows.cpu().numpy()
+    first = 0
+    for k, (name, at, N) in enumerate(parts):
+        v, r = verdict[at:at + 3 * N].reshape(3, N), rows[first:first + N]
+        for column, plane in ((f"gcaps_{name}", 0), (f"tsg_rr_{name}", 1), (f"gcaps_{name}+prio", 2)):
+            out[column][r] = v[plane]
+        first += N if k % 2 else 0  # a group's two parts share its rows
     return out
 
 
