@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="5994828b00330ceae285ad1ff32a0db7c53a3f7b5520774fa839c5028253a394", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=59_620_606, valu_lane_ops=2_782_704_841),
-                            suspend=dict(valu_wave_insts=65_533_821, valu_lane_ops=2_940_865_555)),
-                  "0": dict(busy=dict(valu_wave_insts=386_273_081, valu_lane_ops=22_597_304_845),
-                            suspend=dict(valu_wave_insts=590_277_719, valu_lane_ops=34_524_405_046))})
+    csrc_sha256="a135deb564e469141e7c2a61d93c90e42067471b3b9a340d11ac194d4e48b962", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=57_037_331, valu_lane_ops=2_607_733_669),
+                            suspend=dict(valu_wave_insts=62_009_460, valu_lane_ops=2_706_775_625)),
+                  "0": dict(busy=dict(valu_wave_insts=358_551_067, valu_lane_ops=20_594_273_111),
+                            suspend=dict(valu_wave_insts=535_833_521, valu_lane_ops=30_740_321_925))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="5994828b00330ceae285ad1ff32a0db7c53a3f7b5520774fa839c5028253a394",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915871141, write_bytes=328844555)
+MEASURED_TRAFFIC = dict(csrc_sha256="a135deb564e469141e7c2a61d93c90e42067471b3b9a340d11ac194d4e48b962",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915795763, write_bytes=328837427)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="ab919ed814213007952ddc20641acd550e64db73854fe51598529a312f7a141f",
-                              workload=3, tasksets=1_000_000, fetch_bytes=877836681, write_bytes=242013870)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="bc903ac9c8d740aed4281ba539979a83b515d39e95ed76d84d8ecaddaf7d8055",
+                              workload=3, tasksets=1_000_000, fetch_bytes=877935104, write_bytes=242011904)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged
