@@ -4,7 +4,7 @@ verdict, through the C ABI."""
 import numpy as np
 import pytest
 
-from test_gpu_parity import few_gpu_tasks_workload, gpu, relaxed_workload  # noqa: F401 (fixture)
+from test_gpu_parity import few_gpu_tasks_workload, gpu, no_demand_workload, relaxed_workload  # noqa: F401 (fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +102,31 @@ def test_priority_ties_cpu_only_tasks_and_constrained_deadlines(oracle, gpu):
     batch["core"] = rng.integers(0, 5, batch["core"].shape).astype(np.uint8)
     found = compare(oracle, B, ctx, batch)
     assert found > 300
+
+
+@pytest.mark.parametrize("kernel", ["", "list"])
+@pytest.mark.parametrize("n,S", [(2, 1), (9, 3), (20, 3), (32, 2), (40, 2)])
+@pytest.mark.parametrize("overloaded", [False, True])
+def test_tasks_without_demand_below_overloaded_ones(oracle, monkeypatch, overloaded, n, S, kernel):
+    """A bound of 0 for a task without demand of its own, whatever the utilisation above it: the search and the analysis
+    for given priorities (here the GPU order of the task priorities)."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    if kernel:
+        monkeypatch.setenv("GCAPS_GPRIO_KERNEL", kernel)
+    batch = no_demand_workload(600, n, S, overloaded, seed=90 + n)
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        compare(oracle, B, ctx, batch)
+        zeros = 0
+        for wait in (BUSY, SUSPEND):
+            want_r, want_s = oracle.gprio_rta_batch(batch, batch["prio"], wait)
+            got_r, got_s = B.gcaps_gprio_rta_batch(ctx, batch, wait, batch["prio"])
+            assert np.array_equal(got_r, want_r) and np.array_equal(got_s, want_s), wait
+            zeros += int((want_r == 0).sum())
+        assert zeros > 200
+    finally:
+        B.gcaps_destroy(ctx)
 
 
 def test_values_beyond_24_bits(oracle, gpu):

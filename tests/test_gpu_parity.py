@@ -101,6 +101,52 @@ def test_job_counts_at_the_edges_of_a_period(oracle, gpu, period, n_cores, per_c
     compare_continue(oracle, B, batch)
 
 
+def no_demand_workload(N, n, S, overloaded, seed):
+    """CPU-only tasks without any demand (C = 0, with eps = 0 nothing of their own) among tasks that cost the ones below
+    them on their core more than a period: R = 0 is their bound whatever the utilisation above them is.  Either one
+    GPU-using task per taskset, whose slices and switches (Lemma 4) charge tasks below it 1,224 per period of less
+    than 1,000 while it meets its own deadline, or (`overloaded`) CPU demands of most of a period each."""
+    rng = np.random.default_rng(seed)
+    batch = relaxed_workload(N, seed=seed, n_cores=1, per_core=n, S=S)
+    shape = (N, n)
+    T = rng.integers(300, 1000, shape)
+    C = np.where(rng.random(shape) < 0.6, 0, T * 2 // 3 if overloaded else T // (8 * n) + 1)
+    gpu_task = np.zeros(shape, bool)
+    gpu_task[np.arange(N), rng.integers(0, max(1, n // 2), N)] = True
+    batch["prio"] = np.broadcast_to(n - np.arange(n), shape).astype(np.int32).copy()
+    batch["core"] = rng.integers(0, 2, shape).astype(np.uint8)
+    batch["period_us"] = batch["deadline_us"] = T.astype(np.uint32)
+    batch["cpu_us"] = np.where(gpu_task, 1, C).astype(np.uint32)
+    batch["n_gseg"] = gpu_task.astype(np.uint8)
+    batch["gm_us"] = rng.integers(0, 3, (N, n, S)).astype(np.uint32)
+    batch["ge_us"] = rng.integers(1, 4, (N, n, S)).astype(np.uint32)
+    batch["eps_us"] = np.zeros(N, np.uint32)
+    batch["theta_us"] = np.full(N, 200, np.uint32)
+    batch["slice_us"] = np.full(N, 1024, np.uint32)
+    return batch
+
+
+@pytest.mark.parametrize("env", [{}, {"GCAPS_ONE_LAUNCH": "0"}, {"GCAPS_ONE_LAUNCH": "100000"}, {"GCAPS_DEEP_KERNEL": "lds"}])
+@pytest.mark.parametrize("n,S", [(2, 1), (9, 3), (20, 3), (24, 8), (32, 2), (40, 2)])
+@pytest.mark.parametrize("overloaded", [False, True])
+def test_tasks_without_demand_below_overloaded_ones(oracle, monkeypatch, overloaded, n, S, env):
+    """Every route of the analysis, with and without continue-after-miss, finds the fixed point 0."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    batch = no_demand_workload(600, n, S, overloaded, seed=90 + n)
+    want_r = oracle.rta_batch(batch, RR, BUSY, threads=16, options=oracle.OPT_CONTINUE_AFTER_MISS)[0]
+    assert (want_r == 0).sum() > 100
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        for policy in (GCAPS, RR, BOTH):
+            compare(oracle, B, ctx, batch, policy)
+    finally:
+        B.gcaps_destroy(ctx)
+    compare_continue(oracle, B, batch)
+
+
 def test_priority_ties_and_cpu_only_tasks(oracle, gpu):
     B, ctx, _ = gpu
     rng = np.random.default_rng(5)
