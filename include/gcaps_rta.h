@@ -171,7 +171,7 @@ int gcaps_rta_batch(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wa
  * above.  The work is queued on the context's stream and the call returns
  * without waiting for it.  Argument errors are reported at once; task-model
  * violations are detected on the device and reported by gcaps_status().
- * Outputs of an invalid taskset are undefined, all others are complete.
+ * The verdict of an invalid taskset is 0 and its response times are undefined; the outputs of all others are complete.
  * The launches of a call may be recorded into a HIP graph (stream capture) once a direct call with
  * the same sizes has been made on the context: that call makes the device allocations, a recorded
  * one makes none (GCAPS_ESIZE when it would have to).  A direct call that needs more scratch than any before

@@ -204,6 +204,48 @@ def test_invalid_taskset_is_reported(gpu):
     B.gcaps_rta_batch(ctx, batch, BOTH, BUSY)
 
 
+@pytest.mark.parametrize("env", [{}, {"GCAPS_ONE_LAUNCH": "0"}, {"GCAPS_ONE_LAUNCH": "100000"}, {"GCAPS_DEEP_KERNEL": "lds"}])
+@pytest.mark.parametrize("cores,per_core,S,cont", [(4, 5, 3, 0), (4, 5, 3, 1), (2, 2, 5, 0), (4, 10, 2, 1), (5, 51, 1, 0), (5, 51, 1, 1)])
+def test_verdict_of_an_invalid_taskset_is_0(oracle, monkeypatch, cores, per_core, S, cont, env):
+    """On every route, under every policy: a caller that goes on with the tasksets that failed meets it again."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    batch = relaxed_workload(130, seed=3, n_cores=cores, per_core=per_core, S=S)
+    bad = [0, 17, 63, 64, 129]
+    batch["period_us"][bad[0], 0] = 0
+    batch["deadline_us"][bad[1], -1] = batch["period_us"][bad[1], -1] + 1
+    batch["slice_us"][bad[2]] = 0
+    batch["n_gseg"][bad[3], 1] = S + 1
+    batch["deadline_us"][bad[4], 0] = 0
+    good = np.setdiff1d(np.arange(130), bad)
+    sub = {k: v[good] for k, v in batch.items()}
+    N, n = batch["cpu_us"].shape
+    stream = torch.cuda.Stream()
+    ctx = B.gcaps_create(0, stream.cuda_stream)
+    B.gcaps_set_continue_after_miss(ctx, cont)
+    try:
+        d = B.to_device(batch)
+        for wait in (BUSY, SUSPEND):
+            want_r, want_s, _ = oracle.rta_batch(sub, BOTH, wait, threads=16,
+                                                 options=oracle.OPT_CONTINUE_AFTER_MISS if cont else 0)
+            for policy, planes in ((GCAPS, [0]), (RR, [1]), (BOTH, [0, 1])):
+                P = B.npol(policy)
+                d_resp = torch.full((P, N, n), -7, dtype=torch.int64, device="cuda:0")
+                d_sched = torch.full((P, N), 1, dtype=torch.uint8, device="cuda:0")
+                torch.cuda.synchronize()
+                B.gcaps_rta_batch_device(ctx, d, policy, wait, d_resp, d_sched)
+                with pytest.raises(B.GcapsError) as e:
+                    B.gcaps_status(ctx)
+                assert e.value.code == B.GCAPS_ETASK and e.value.first_bad == 0
+                got = d_sched.cpu().numpy()
+                assert (got[:, bad] == 0).all(), (policy, wait)
+                assert (got[:, good] == want_s[planes]).all() and (d_resp.cpu().numpy()[:, good] == want_r[planes]).all()
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_device_entry_point_matches_host_entry_point(oracle, gpu):
     import torch
     from paper_2406_05221_amd import taskgen

@@ -129,6 +129,30 @@ def test_sweep_matches_the_oracle(oracle, gpu):
         assert shares["gcaps_suspend+prio"] >= shares["gcaps_suspend"]
 
 
+def test_sweep_point_reports_an_invalid_taskset(gpu, monkeypatch):
+    """verdicts_device reads the status of a group's last call, the search of the tasksets without a verdict of 1: an
+    invalid taskset among valid ones is reported on both routes of the analysis, whatever the buffers held before."""
+    import torch
+    from paper_2406_05221_amd import binding as B, sweep
+    for one_launch in ("0", "100000"):
+        monkeypatch.setenv("GCAPS_ONE_LAUNCH", one_launch)
+        ctx = B.gcaps_create(0, torch.cuda.current_stream().cuda_stream)
+        try:
+            groups = B.gcaps_table3_device(ctx, 900, seed=9, util=(0.2, 0.2))
+            n = max(groups, key=lambda m: groups[m][0].numel())
+            row = groups[n][0].numel() // 2
+            sweep.verdicts_device(ctx, groups, 900)
+            groups[n][1]["period_us"][row, 1] = 0
+            ones = torch.ones(6 * 900, dtype=torch.uint8, device="cuda:0")
+            torch.cuda.synchronize()
+            del ones  # its memory is the next allocation of this size
+            with pytest.raises(B.GcapsError) as e:
+                sweep.verdicts_device(ctx, groups, 900)
+            assert e.value.code == B.GCAPS_ETASK and e.value.first_bad == row
+        finally:
+            B.gcaps_destroy(ctx)
+
+
 def test_sweep_with_best_effort_tasks_matches_the_oracle(oracle, gpu):
     from paper_2406_05221_amd import sweep, taskgen
     B, ctx, _ = gpu
