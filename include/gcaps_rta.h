@@ -178,7 +178,8 @@ int gcaps_rta_batch(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wa
  * it frees and reallocates the context's buffers: graphs recorded earlier on this context then point
  * to freed memory and must be recorded again.  A recorded call depends on no earlier call and can be
  * replayed any number of times, with direct calls in between.  The same holds for the other device-resident entry points
- * (gcaps_gprio_assign_batch_device, gcaps_gprio_rta_batch_device, gcaps_simulate_batch_device).
+ * (gcaps_gprio_assign_batch_device, gcaps_gprio_rta_batch_device); recorded simulations use no such scratch, see
+ * gcaps_simulate_batch.
  */
 int gcaps_rta_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wait_mode,
                            int64_t *d_out_resp, uint8_t *d_out_sched);
@@ -310,6 +311,9 @@ int gcaps_gprio_rta_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, int w
  *              simulation of that taskset stops there and its outputs hold what had completed until then
  * Limits: n_tasks <= 32 (else GCAPS_EINVAL); a taskset with T = 0, L = 0, eta^g > S or a core index >= 64
  * makes the call fail with GCAPS_ETASK (smallest index; outputs unspecified).
+ * A recorded call uses no scratch that another call could grow: it needs no direct call before it, and its graph stays
+ * valid whatever the context does afterwards.  (A direct call hands the tasksets out longest schedule first, from a
+ * list of 12 bytes per taskset that the context keeps; a recorded one in caller order.)
  * One lane simulates one taskset under one policy and jumps from event to event (end of a segment, slice,
  * switch or update; a release).  gcaps_simulate_batch takes HOST pointers and returns when the results are in
  * place; gcaps_simulate_batch_device takes DEVICE pointers, queues the work on the context's stream and

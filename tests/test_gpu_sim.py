@@ -312,6 +312,46 @@ def test_captured_simulation_replays(oracle, monkeypatch):
         B.gcaps_destroy(ctx)
 
 
+def test_recorded_simulation_outlives_larger_calls(oracle, monkeypatch):
+    """A recorded simulation uses no buffer of the context that a later call may replace: recorded with no call before
+    it, replayed after a larger direct simulation and a larger analysis with its list ordered, both of which allocate."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    monkeypatch.setenv("GCAPS_SIM_BLOCKS", "5")
+    stream = torch.cuda.Stream()
+    ctx = B.gcaps_create(0, stream.cuda_stream)
+    try:
+        batch, larger = small_batch(1500, seed=43, util=(0.2, 0.8)), small_batch(9000, seed=44)
+        d = B.to_device(batch)
+        N, n = batch["cpu_us"].shape
+        mort = torch.empty((2, N, n), dtype=torch.int64, device="cuda:0")
+        jobs = torch.empty((2, N, n), dtype=torch.int32, device="cuda:0")
+        flag = torch.empty((2, N), dtype=torch.uint8, device="cuda:0")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.gcaps_simulate_batch_device(ctx, d, BOTH, BUSY, 2000, mort, jobs, flag)
+        want = oracle.simulate_batch(batch, BOTH, BUSY, 2000, threads=16)
+        ref = oracle.simulate_batch(larger, GCAPS, SUSPEND, 500, threads=16)
+        for k in range(3):
+            mort.fill_(-7)
+            jobs.fill_(9)
+            flag.fill_(9)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert (mort.cpu().numpy() == want[0]).all() and (flag.cpu().numpy() == want[2]).all(), k
+            assert (jobs.cpu().numpy().view(np.uint32) == want[1]).all(), k
+            sub = {name: v[:3000 * (k + 1)] for name, v in larger.items()}
+            got = B.gcaps_simulate_batch(ctx, sub, GCAPS, SUSPEND, 500)
+            assert all((g == w[:, :3000 * (k + 1)]).all() for g, w in zip(got, ref)), k
+            B.gcaps_set_binning(ctx, 1)
+            B.gcaps_rta_batch(ctx, sub, BOTH, BUSY)
+            B.gcaps_set_binning(ctx, 0)
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_bench_size_on_sampled_tasksets(oracle, gpu):
     """The batch size and launch configuration that bench.py times (262,144 tasksets of its recipe: more than
     the lanes that are resident at once), over a tenth of a second of task time; the oracle follows a sample spread over
