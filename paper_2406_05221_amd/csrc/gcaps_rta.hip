@@ -25,6 +25,7 @@
 #include "gprio_fast.hip.inc"
 #include "gprio_tile.hip.inc"
 #include "gprio_given.hip.inc"
+#include "small_quotient.hip.inc"
 #include "sim.hip.inc"
 #include "taskgen_device.hip.inc"
 #include "taskgen_table3.hip.inc"

@@ -156,6 +156,24 @@ def test_large_values(oracle, gpu):
     compare(oracle, B, ctx, batch, 2000, offset=off)
 
 
+@pytest.mark.parametrize("lo,hi", [(1, 300), (2**20 - 40, 2**20 + 40), (2**21 - 40, 2**21 + 40), (2**21, 2**22), (2**31 - 40, 2**31 - 1)])
+def test_large_cpu_times_are_dealt_out_whole(gpu, lo, hi):
+    """A task alone on its core with empty GPU segments responds after exactly C, whatever number of parts C is dealt to:
+    the parts add up on both sides of the range in which the quotient is taken in floats."""
+    B, ctx, _ = gpu
+    rng = np.random.default_rng(lo)
+    N, n, S = 40, 8, 5
+    C = rng.integers(lo, hi + 1, (N, n)).astype(np.uint32)
+    T = np.full((N, n), 2**32 - 1, np.uint32)
+    batch = dict(theta_us=np.zeros(N, np.uint32), eps_us=np.zeros(N, np.uint32), slice_us=np.full(N, 9, np.uint32), cpu_us=C,
+                 period_us=T, deadline_us=T, prio=np.tile(np.arange(n, dtype=np.int32), (N, 1)),
+                 core=np.tile(np.arange(n, dtype=np.uint8), (N, 1)), n_gseg=rng.integers(0, S + 1, (N, n)).astype(np.uint8),
+                 gm_us=np.zeros((N, n, S), np.uint32), ge_us=np.zeros((N, n, S), np.uint32))
+    for wait in (BUSY, SUSPEND):
+        mort, jobs, flag = B.gcaps_simulate_batch(ctx, batch, BOTH, wait, 2**31)
+        assert (mort == C).all() and (jobs == 1).all() and (flag == 0).all()
+
+
 def test_invalid_arguments(gpu):
     B, ctx, _ = gpu
     batch = small_batch(300, seed=13)
