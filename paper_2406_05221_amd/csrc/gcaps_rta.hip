@@ -250,6 +250,7 @@ __global__ void reset_status_kernel(u32 *status, int first_chunk) {
     }
     status[1] = 0; /* length of the list for the 64-bit kernel */
     status[2] = 0; /* length of the ordered list for the second fast launch (binning only) */
+    status[6] = 0; /* schedules too short to be put in order */
   }
   status[fast::ST_DEEP_COUNTS + threadIdx.x] = 0; /* per-region lengths of the list for the second fast launch */
   for (u32 k = threadIdx.x; k < fast::kOrderBuckets; k += blockDim.x) status[fast::ST_ORDER_HIST + k] = 0;
@@ -779,19 +780,21 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
   });
 }
 
-/* The longest schedules first; null (caller order) where there is no memory for the list, or where the stream is
- * recording: a recorded simulation uses nothing but the status block, which stays where it is as long as the context
+/* The longest schedules first; null (caller order) where there is no memory for the list, for a few tasks (schedules
+ * short enough for the sort and the scattered reads behind it to show: 65,536 tasksets of 6 tasks, a horizon of 200,000,
+ * 2.49 ms in caller order, 2.72 by length), or where the stream is recording: a recorded simulation uses nothing but the status block, which stays where it is as long as the context
  * lives, so that it can be replayed whatever calls grow the context's buffers afterwards (65,536 tasksets of 20 tasks,
  * a second of task time: 45 ms by length, 54 in caller order). */
 const u32 *simulation_order(gcaps_ctx *ctx, const gcaps_batch *sub, u32 horizon) {
   const u32 N = sub->n_tasksets, blocks = (N + 255u) / 256u;
-  if (ctx->capturing || ctx->pool.sim_order.reserve((size_t)N * 3 * sizeof(u32)) != GCAPS_OK) return nullptr;
+  if (sub->n_tasks <= sim::kFewTasks || ctx->capturing) return nullptr;
+  if (ctx->pool.sim_order.reserve((size_t)N * 3 * sizeof(u32)) != GCAPS_OK) return nullptr;
   u32 *order = (u32 *)ctx->pool.sim_order.ptr, *bucket = order + N, *position = bucket + N;
   u32 *hist = status_of(ctx) + fast::ST_ORDER_HIST;
   hipLaunchKernelGGL(sim::order_count_kernel, dim3(blocks), dim3(256), 0, ctx->stream, *sub, (float)horizon, hist,
-                     bucket, position);
+                     bucket, position, status_of(ctx) + sim::kStatusShort);
   hipLaunchKernelGGL(sim::order_kernel, dim3(blocks), dim3(256), 0, ctx->stream, N, (const u32 *)hist,
-                     (const u32 *)bucket, (const u32 *)position, order);
+                     (const u32 *)bucket, (const u32 *)position, order, (const u32 *)status_of(ctx) + sim::kStatusShort);
   return order;
 }
 
@@ -835,13 +838,18 @@ int run_simulate(gcaps_ctx *ctx, const gcaps_batch *b, const uint32_t *d_offset,
       return wait_mode == GCAPS_WAIT_BUSY ? go(std::true_type{}, lanes) : go(std::false_type{}, lanes);
     };
     /* Lanes per wavefront: few while that leaves at most 16 wavefronts per CU, for a step takes the longer the more
-     * lanes take part; full half-wavefronts beyond, where the chip is busy.  20 tasks, both policies, 4 / 8 / 16 / 32
-     * lanes: 1,000 tasksets 23 / 25 / 30 / 35 ms, 8,192 23 / 31 / 35 / 37, 16,384 34 / 27 / 33 / 40, 65,536
-     * 97 / 66 / 48 / 45 (64 lanes: 49, the columns of fewer wavefronts fit the LDS). */
-    const u64 schedules = (u64)sub->n_tasksets * (policy == GCAPS_POLICY_BOTH ? 2u : 1u), most = (u64)ctx->n_cu * 16u;
+     * lanes take part; full half-wavefronts beyond, where the chip is busy (64 lanes: the columns of fewer wavefronts
+     * fit the LDS).  20 tasks, a second, both policies, 4 / 8 / 16 / 32 lanes: 1,000 tasksets 23 / 25 / 30 / 35 ms,
+     * 8,192 23 / 31 / 35 / 37, 16,384 34 / 27 / 33 / 40, 65,536 97 / 66 / 48 / 45 (64: 49).  The columns of few tasks leave
+     * room for all, and their steps differ less from lane to lane: 200,000 tasksets of 3 / 6 / 8 tasks, a horizon of 2,000, 137 / 240 /
+     * 398 us with 64 lanes, 217 / 335 / 461 with 32; 5,000 of 1 / 3 tasks, GCAPS, 20,000, 34 / 91 us with 16 lanes, 46 / 112 with 4. */
+    const u32 nt = sub->n_tasks;
+    const u64 schedules = (u64)sub->n_tasksets * (policy == GCAPS_POLICY_BOTH ? 2u : 1u);
+    const u64 most = (u64)ctx->n_cu * (nt <= sim::kFewTasks / 2u ? 2u : nt <= sim::kFewTasks ? 8u : 16u);
     if (schedules <= 4u * most) return with(std::integral_constant<int, 4>{});
     if (schedules <= 8u * most) return with(std::integral_constant<int, 8>{});
     if (schedules <= 16u * most) return with(std::integral_constant<int, 16>{});
+    if (schedules > 32u * most && nt <= sim::kFewTasks) return with(std::integral_constant<int, 64>{});
     return with(std::integral_constant<int, 32>{});
   });
 }

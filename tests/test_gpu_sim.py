@@ -270,6 +270,46 @@ def test_lanes_take_further_tasksets(oracle, monkeypatch):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("cores,per_core,horizon", [(1, 1, 60), (1, 3, 700), (2, 4, 40), (3, 4, 30), (3, 4, 2500), (6, 4, 90),
+                                                    (16, 2, 25), (16, 2, 1500), (32, 1, 400), (5, 2, 3000)])
+def test_short_and_long_schedules_dealt_to_few_lanes(oracle, monkeypatch, cores, per_core, horizon):
+    """Two workgroups deal out 3,000 tasksets: schedules of a few steps a wavefront at a time, long ones to some lanes
+    while others run; in caller order (few tasks, or few phases before the horizon) and by length; invalid tasksets
+    among them and cores beyond the four held in registers."""
+    import torch
+    from paper_2406_05221_amd import binding as B, taskgen
+    monkeypatch.setenv("GCAPS_SIM_BLOCKS", "2")
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        batch = taskgen.generate(3000, n_cores=cores, tasks_per_core=per_core, max_gseg=2, util=(0.1, 0.9), eta=(0, 2),
+                                 share=(0.1, 0.5), period=(40, 400), overhead=(0, 3), slice_us=8, seed=horizon, stream=52)
+        off = np.random.default_rng(horizon).integers(0, 60, batch["cpu_us"].shape).astype(np.uint32)
+        for wait, policy, offset in ((BUSY, BOTH, None), (SUSPEND, GCAPS, off), (SUSPEND, RR, off)):
+            want = oracle.simulate_batch(batch, policy, wait, horizon, offset=offset, threads=16)
+            got = B.gcaps_simulate_batch(ctx, batch, policy, wait, horizon, offset=offset)
+            assert all((g == w).all() for g, w in zip(got, want)), (wait, policy)
+        bad = {k: v.copy() for k, v in batch.items()}
+        bad["period_us"][[5, 1700, 2999], 0] = 0
+        good = np.setdiff1d(np.arange(3000), [5, 1700, 2999])
+        with pytest.raises(B.GcapsError) as e:
+            B.gcaps_simulate_batch(ctx, bad, RR, BUSY, horizon)
+        assert e.value.first_bad == 5
+        d = B.to_device(bad)
+        n = cores * per_core
+        mort = torch.empty((1, 3000, n), dtype=torch.int64, device="cuda:0")
+        jobs = torch.empty((1, 3000, n), dtype=torch.int32, device="cuda:0")
+        flag = torch.empty((1, 3000), dtype=torch.uint8, device="cuda:0")
+        torch.cuda.synchronize()
+        B.gcaps_simulate_batch_device(ctx, d, RR, BUSY, horizon, mort, jobs, flag)
+        with pytest.raises(B.GcapsError):
+            B.gcaps_status(ctx)
+        want = oracle.simulate_batch({k: v[good] for k, v in batch.items()}, RR, BUSY, horizon, threads=16)
+        for g, w in zip((mort, jobs, flag), want):
+            assert (g.cpu().numpy().astype(np.int64)[:, good] == w.astype(np.int64)).all()
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 @pytest.mark.parametrize("N,cores,per_core,horizon", [(1, 1, 1, 3000), (3, 8, 4, 2000), (1031, 6, 5, 900),
                                                       (8193, 5, 3, 300), (20_001, 2, 2, 300), (70_003, 1, 3, 200)])
 def test_lane_counts_and_core_counts(oracle, gpu, N, cores, per_core, horizon):
