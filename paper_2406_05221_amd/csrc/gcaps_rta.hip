@@ -472,12 +472,6 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
     ctx->wide_only = n > fast::kMaxTasks || fast::deep_lds_bytes(n, ctx->deep_lanes) > (size_t)ctx->lds_limit;
   if (ctx->wide_only) return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, nullptr, nullptr, N);
   int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
-  /* tiles of the first launch go to the list regions round-robin: a region never overflows */
-  const u32 producer_tiles = (N + 15u) / 16u; /* the narrowest tile width */
-  ctx->region_cap = ((producer_tiles + fast::kListRegions - 1) / fast::kListRegions) * 64u;
-  if (rc == GCAPS_OK) rc = ctx->pool.deep_list.reserve((size_t)ctx->region_cap * fast::kListRegions * sizeof(u32), !ctx->capturing);
-  if (rc == GCAPS_OK && ctx->binning)
-    rc = ctx->pool.deep_aux.reserve((size_t)ctx->region_cap * fast::kListRegions * 2 * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
 
   if (ctx->cont || one_launch_applies(ctx, b)) {
@@ -490,6 +484,13 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
                        N < 65536u ? N : 65536u);
   }
 
+  /* tiles of the first launch go to the list regions round-robin: a region never overflows */
+  const u32 producer_tiles = (N + 15u) / 16u; /* the narrowest tile width */
+  ctx->region_cap = ((producer_tiles + fast::kListRegions - 1) / fast::kListRegions) * 64u;
+  rc = ctx->pool.deep_list.reserve((size_t)ctx->region_cap * fast::kListRegions * sizeof(u32), !ctx->capturing);
+  if (rc == GCAPS_OK && ctx->binning)
+    rc = ctx->pool.deep_aux.reserve((size_t)ctx->region_cap * fast::kListRegions * 2 * sizeof(u32), !ctx->capturing);
+  if (rc != GCAPS_OK) return rc;
   /* first launch: every taskset, the kr highest-priority tasks only */
   const u32 tiles = (N + (u32)ts_screen - 1) / (u32)ts_screen;
   rc = ts_screen == 64 ? launch_fast<64>(ctx, b, policy, wait_mode, d_resp, d_sched, kr, tiles)

@@ -659,6 +659,38 @@ def test_recorded_call_that_would_have_to_allocate_is_refused(oracle, gpu):
         B.gcaps_destroy(ctx)
 
 
+def test_recorded_call_in_one_launch_needs_no_list(oracle, monkeypatch):
+    """A call that takes one launch has no list between launches and is not refused for the room it would take: recorded
+    after a priority search of the same size, which makes the other allocations."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    monkeypatch.setenv("GCAPS_ONE_LAUNCH", "100000")
+    stream = torch.cuda.Stream()
+    ctx = B.gcaps_create(0, stream.cuda_stream)
+    try:
+        batch = relaxed_workload(3_000, seed=63)
+        B.gcaps_gprio_assign_batch(ctx, batch, BUSY)
+        d = B.to_device(batch)
+        N, n = batch["cpu_us"].shape
+        d_resp = torch.empty((2, N, n), dtype=torch.int64, device="cuda:0")
+        d_sched = torch.empty((2, N), dtype=torch.uint8, device="cuda:0")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.gcaps_rta_batch_device(ctx, d, BOTH, BUSY, d_resp, d_sched)
+        want_r, want_s, _ = oracle.rta_batch(batch, BOTH, BUSY, threads=16)
+        for k in range(3):
+            d_resp.fill_(-7)
+            d_sched.fill_(9)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(d_resp.cpu().numpy(), want_r) and np.array_equal(d_sched.cpu().numpy(), want_s), k
+            B.gcaps_rta_batch(ctx, relaxed_workload(700, seed=k), BOTH, SUSPEND)
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_argument_and_allocation_failures_leave_the_context_usable(oracle, gpu):
     """Failures forced from the host: an empty batch (GCAPS_EINVAL) and a batch whose device copy cannot be
     allocated (GCAPS_ENOMEM: the sizes ask for petabytes; no array is touched before the allocation fails)."""
