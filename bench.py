@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="1d81315fd73f437dff2b4d3266b2fbc6f9d1dfd9fdddc4c7ff1e9c2db53e0139", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=56_946_643, valu_lane_ops=2_597_810_419),
-                            suspend=dict(valu_wave_insts=61_962_541, valu_lane_ops=2_699_448_313)),
-                  "0": dict(busy=dict(valu_wave_insts=355_108_693, valu_lane_ops=20_370_633_653),
-                            suspend=dict(valu_wave_insts=529_809_112, valu_lane_ops=30_352_411_770))})
+    csrc_sha256="e6cf53f0fc60f8550874623a8a1efdc7da1b49271630b8dd495b854818d010bc", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=56_954_704, valu_lane_ops=2_598_291_533),
+                            suspend=dict(valu_wave_insts=61_934_984, valu_lane_ops=2_697_817_807)),
+                  "0": dict(busy=dict(valu_wave_insts=355_113_225, valu_lane_ops=20_370_891_972),
+                            suspend=dict(valu_wave_insts=529_786_483, valu_lane_ops=30_351_120_037))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="1d81315fd73f437dff2b4d3266b2fbc6f9d1dfd9fdddc4c7ff1e9c2db53e0139",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915650449, write_bytes=328823116)
+MEASURED_TRAFFIC = dict(csrc_sha256="e6cf53f0fc60f8550874623a8a1efdc7da1b49271630b8dd495b854818d010bc",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915840727, write_bytes=328825386)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="6bd1325abacd269908dc41f95b4840f1cf85151b5b99b1970d0e32a72a46a8c6",
-                              workload=3, tasksets=1_000_000, fetch_bytes=877942749, write_bytes=242012668)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="9a7f111d7b9132efd421532c37695c56b655419beb060ecd888e3522a334dcea",
+                              workload=3, tasksets=1_000_000, fetch_bytes=877998749, write_bytes=242012499)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged

@@ -133,7 +133,7 @@ enum {
  *   GCAPS_SCREEN_TASKS    tasks per taskset that the first launch analyses (default 4)
  *   GCAPS_DEEP_LANES      lanes per taskset in the second launch, 4 (default) or 8
  *   GCAPS_ONE_LAUNCH      analysis calls of at most this many tasksets (shapes of at most 32 tasks and eight
- *                         segments) take one full-depth launch instead of two (0: none; default: by size and shape)
+ *                         segments) take one full-depth launch instead of two (0: none; default: by size, shape and policy)
  *   GCAPS_CHUNK_TASKSETS  cap on the tasksets per internal chunk of a call
  *   GCAPS_DEEP_KERNEL     "lds": the second launch of the analysis keeps its term records in LDS for every
  *                         shape (default: in registers for shapes of at most 32 tasks)

@@ -414,19 +414,28 @@ bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
 }
 
 /* One full-depth launch for the whole call instead of two with a list between them.  A small call is bound by latency:
- * the chain of dependent loads of a launch, and a second launch behind it; a large one by work, most of which the first
- * launch of the two saves where most tasksets miss within their first ranks.  The line lies where the elements of the
- * call fill the chip twice over.  us in two launches / in one, both policies, self-suspension:
- *   6 tasks x 1 segment, 1,000 tasksets: 27.5 / 16.0;  16 x 3, 9,000: 33.9 / 23.5, 30,000: 40.0 / 32.4, 65,536: 44.3 / 46.0;
- *   20 x 3, 1,000 / 16,000 / 65,536: 37.1 / 25.3, 53.3 / 41.9, 60.8 / 63.8; lightly loaded 58.5 / 42.6, 67.5 / 49.4, 109.6 / 86.1;
- *   24 x 4 settled by the first ranks, 1,000 / 16,384 / 32,768: 20.8 / 19.5, 29.7 / 26.2, 32.2 / 33.9.
- * Beyond 24 tasks one launch gives less on lightly loaded tasksets (28 x 3, 1,000: 83.7 / 65.8) and loses more on
- * overloaded ones (32 x 5, 1,000 / 16,384: 23.2 / 27.8, 27.0 / 37.7: seven or eight rounds of elements to stage). */
-bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
+ * the chain of dependent loads of a launch, and a second launch behind it.  A large one is bound by work, most of which
+ * the first launch of the two saves where tasksets miss their deadlines within its ranks; it stages no segments of further
+ * ranks.  How many do is not known here: the lines lie where a batch that misses at once (periods from 500, overheads of
+ * 300, half to nine tenths of every core used; the round-robin pass alone always does) takes as long either way, on
+ * inputs that were just analysed and on inputs that were not in any cache.  us in two launches / in one, both
+ * policies, self-suspension, such a batch; then a lightly loaded one:
+ *   6 tasks x 1 segment, 1,000 tasksets 25.9 / 15.4, 28.7 / 16.9; 16,000 27.1 / 20.1, 38.2 / 23.8 (20,000);
+ *   16 x 3, 8,000 22.0 / 16.7, 55.4 / 39.0 (9,000); 16,000 22.8 / 19.0, 32,768 24.0 / 25.5;
+ *   20 x 3, 8,000 21.2 / 17.5, 66.3 / 48.3 (9,000); 19,660 22.6 / 22.0, cold 26.4 / 28.8;
+ *   24 x 3, 8,000 21.6 / 20.2; 24 x 4, 10,922 21.7 / 22.3; 24 x 8, 5,461 22.3 / 25.9 (segments through registers, eight
+ *   slots a task: the time to stage them shows from 64 slots a taskset on);
+ *   8 x 1 on eight cores, 32,768 16.5 / 21.8; 3 x 1 on three, 12,288 13.6 / 15.1.
+ * The round-robin pass alone takes half the time in two launches: 20 x 3, 6,553 14.8 / 14.3, 13,107 15.9 / 17.1.  One or two
+ * tasks are settled by the first launch of the two alone: 10.8 / 11.5 with 1,000 tasksets. */
+bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b, int policy) {
   if (ctx->binning || ctx->screen_tasks != 4u || !quad_all_applies(ctx, b)) return false;
   if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
-  return b->n_tasks <= 24u && b->n_tasksets <= (u32)ctx->n_cu * 128u &&
-         (u64)b->n_tasksets * b->n_tasks <= (u64)ctx->n_cu * 2048u;
+  const u32 n = b->n_tasks, cu = (u32)ctx->n_cu;
+  const bool many_slots = b->max_gseg > 3u;
+  if (n < 3u || n > 24u || (many_slots && n * b->max_gseg > 64u)) return false;
+  const u64 tasksets = (u64)b->n_tasksets * (policy == GCAPS_POLICY_RR ? 2u : 1u);
+  return tasksets <= cu * (n <= 5u || many_slots ? 32u : 64u) && tasksets * n <= cu * (many_slots ? 384u : 768u);
 }
 
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
@@ -474,7 +483,7 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
   int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
 
-  if (ctx->cont || one_launch_applies(ctx, b)) {
+  if (ctx->cont || one_launch_applies(ctx, b, policy)) {
     /* continue-after-miss: nothing is settled early, the full-depth launch takes every taskset */
     rc = quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
                                   : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);

@@ -397,6 +397,17 @@ def test_calls_in_one_launch_and_in_two(oracle, monkeypatch, shape, tasksets):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("cores,per_core,S,N", [(1, 2, 1, 1_000), (1, 3, 1, 8_192), (1, 5, 4, 8_192), (2, 3, 3, 16_384), (4, 4, 3, 12_288),
+                                                (4, 4, 4, 6_144), (4, 6, 3, 8_192), (5, 5, 3, 1_000), (4, 5, 4, 1_000)])
+def test_default_route_at_its_lines(oracle, gpu, cores, per_core, S, N):
+    """The largest call of a shape that takes one launch by default and one taskset more (both policies; round-robin alone
+    takes half as many), shapes that never do: the same results."""
+    B, ctx, _ = gpu
+    batch = relaxed_workload(N + 1, seed=N, n_cores=cores, per_core=per_core, S=S)
+    for policy, size in ((BOTH, N), (BOTH, N + 1), (RR, N // 2), (RR, N // 2 + 1)):
+        compare(oracle, B, ctx, {k: v[:size] for k, v in batch.items()}, policy, waits=(SUSPEND,))
+
+
 def test_out_of_range_values_below_the_screened_ranks(oracle, gpu):
     """Values outside the fast kernels' range in LOW-priority tasks only: the first launch does not
     look at them, the second hands the taskset over to the 64-bit kernel when it gets there."""
