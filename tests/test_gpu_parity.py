@@ -19,6 +19,19 @@ def gpu():
     B.gcaps_destroy(ctx)
 
 
+@pytest.fixture(params=["0", "100000"], ids=["two_launches", "one_launch"])
+def route(request, gpu, monkeypatch):
+    """The same on a context of its own whose analysis calls all take two launches, or all take one where the shape allows
+    it: by default a call of these sizes takes one of them only."""
+    import torch
+    monkeypatch.setenv("GCAPS_ONE_LAUNCH", request.param)
+    B = gpu[0]
+    stream = torch.cuda.Stream()
+    ctx = B.gcaps_create(0, stream.cuda_stream)
+    yield B, ctx, stream
+    B.gcaps_destroy(ctx)
+
+
 def compare(oracle, B, ctx, batch, policy=BOTH, waits=(BUSY, SUSPEND)):
     for wait in waits:
         want_r, want_s, _ = oracle.rta_batch(batch, policy, wait, threads=16)
@@ -29,9 +42,9 @@ def compare(oracle, B, ctx, batch, policy=BOTH, waits=(BUSY, SUSPEND)):
 
 
 @pytest.mark.parametrize("k,N", [(1, None), (2, None), (3, 20_000), (4, 3_000), (5, 21_600)])
-def test_named_workloads(oracle, gpu, k, N):
+def test_named_workloads(oracle, route, k, N):
     from paper_2406_05221_amd import taskgen
-    B, ctx, _ = gpu
+    B, ctx, _ = route
     print(f"workload {k} N={N}", flush=True)
     compare(oracle, B, ctx, taskgen.config(k, N))
     # the named workloads fit the 24-bit fast kernel entirely
@@ -56,8 +69,8 @@ def few_gpu_tasks_workload(N, seed):
 
 
 @pytest.mark.parametrize("policy", [GCAPS, RR, BOTH])
-def test_mostly_schedulable_tasksets(oracle, gpu, policy):
-    B, ctx, _ = gpu
+def test_mostly_schedulable_tasksets(oracle, route, policy):
+    B, ctx, _ = route
     batch = relaxed_workload(5_003, seed=policy)
     want_s = oracle.rta_batch(batch, GCAPS, SUSPEND, threads=16)[1]
     assert 0.2 < want_s.mean() < 0.98
@@ -71,8 +84,8 @@ def test_mostly_schedulable_tasksets(oracle, gpu, policy):
 
 @pytest.mark.parametrize("shape", [(1, 1, 0), (1, 1, 1), (2, 1, 2), (3, 7, 1), (8, 10, 5), (5, 51, 2), (2, 3, 11),
                                    (3, 11, 7), (2, 17, 4), (4, 16, 3)])
-def test_shapes_and_ragged_batches(oracle, gpu, shape):
-    B, ctx, _ = gpu
+def test_shapes_and_ragged_batches(oracle, route, shape):
+    B, ctx, _ = route
     cores, per_core, S = shape
     for N in (1, 63, 64, 65, 257):
         batch = relaxed_workload(N, seed=N, n_cores=cores, per_core=per_core, S=S)
@@ -81,10 +94,10 @@ def test_shapes_and_ragged_batches(oracle, gpu, shape):
 
 @pytest.mark.parametrize("n_cores,per_core,S", [(4, 5, 3), (3, 8, 4), (2, 16, 5)])
 @pytest.mark.parametrize("period", [(257, 259), (510, 514), (65_535, 65_538), (2**21 - 3, 2**21)])
-def test_job_counts_at_the_edges_of_a_period(oracle, gpu, period, n_cores, per_core, S):
+def test_job_counts_at_the_edges_of_a_period(oracle, route, period, n_cores, per_core, S):
     """Response times that end on and one beside a multiple of a period, at the ends of the range of periods and around
     powers of two, where the reciprocals round differently.  Exact integers: no tolerance."""
-    B, ctx, _ = gpu
+    B, ctx, _ = route
     rng = np.random.default_rng(period[0] + S)
     batch = relaxed_workload(2_000, seed=41, n_cores=n_cores, per_core=per_core, S=S)
     n = batch["cpu_us"].shape[1]
@@ -147,8 +160,8 @@ def test_tasks_without_demand_below_overloaded_ones(oracle, monkeypatch, overloa
     compare_continue(oracle, B, batch)
 
 
-def test_priority_ties_and_cpu_only_tasks(oracle, gpu):
-    B, ctx, _ = gpu
+def test_priority_ties_and_cpu_only_tasks(oracle, route):
+    B, ctx, _ = route
     rng = np.random.default_rng(5)
     batch = relaxed_workload(2_000, seed=9)
     batch["prio"] = rng.integers(-3, 4, batch["prio"].shape).astype(np.int32)
@@ -158,9 +171,9 @@ def test_priority_ties_and_cpu_only_tasks(oracle, gpu):
     compare(oracle, B, ctx, batch)
 
 
-def test_values_beyond_24_bits(oracle, gpu):
+def test_values_beyond_24_bits(oracle, route):
     """Periods of hours, nanosecond-like slices, overheads near 2^32: exact all the same."""
-    B, ctx, _ = gpu
+    B, ctx, _ = route
     rng = np.random.default_rng(6)
     batch = relaxed_workload(1_500, seed=3, n_cores=2, per_core=4, S=2)
     scale = rng.choice([1, 1, 300, 4000], size=(1500, 1)).astype(np.uint64)
@@ -426,11 +439,11 @@ def test_out_of_range_values_below_the_screened_ranks(oracle, gpu):
     assert B.gcaps_last_wide_count(ctx) > 0
 
 
-def test_outputs_at_8_byte_alignment_only(oracle, gpu):
+def test_outputs_at_8_byte_alignment_only(oracle, route):
     """Response buffers that are 8- but not 16-byte aligned (a view into a larger buffer), with
     even and odd task counts: the kernels may use wider stores only where they are aligned."""
     import torch
-    B, ctx, _ = gpu
+    B, ctx, _ = route
     for per_core in (5, 3):  # n = 20, n = 9
         batch = relaxed_workload(1_111, seed=51, n_cores=4 if per_core == 5 else 3, per_core=per_core, S=3)
         d = B.to_device(batch)
@@ -448,13 +461,13 @@ def test_outputs_at_8_byte_alignment_only(oracle, gpu):
             assert (raw[:shift] == -7).all() and (raw[shift + 2 * N * n:] == -7).all()  # nothing outside the view
 
 
-def test_inputs_at_element_alignment_only(oracle, gpu):
+def test_inputs_at_element_alignment_only(oracle, route):
     """Every input array starts one element into a larger buffer: 4-byte aligned words, 1-byte aligned bytes.  The
     kernels load several segment slots of a task with one instruction and stream arrays with wide accesses; none of
     it may assume more than the element's own alignment.  Shapes with 1 to 5 segment slots, both entry points of the
     analysis and the priority search."""
     import torch
-    B, ctx, _ = gpu
+    B, ctx, _ = route
 
     def shifted(batch):
         out = {}
@@ -487,10 +500,10 @@ def test_inputs_at_element_alignment_only(oracle, gpu):
             assert (g_sched.cpu().numpy() == ws).all(), (S, wait)
 
 
-def test_priorities_that_look_like_internal_marks(oracle, gpu):
+def test_priorities_that_look_like_internal_marks(oracle, route):
     """Any int32 is a legal priority.  Values around 2^30 (the first launch marks looked-up tasks
     with such words in the priority column) and the extremes must not confuse anything."""
-    B, ctx, _ = gpu
+    B, ctx, _ = route
     rng = np.random.default_rng(12)
     batch = relaxed_workload(3_000, seed=61)
     odd = rng.choice([2**30, 2**30 + 1, 2**30 + 2, 2**30 + 3, -(2**31), 2**31 - 1, 2**22, -(2**22) - 1],
@@ -599,41 +612,37 @@ def test_continue_after_miss_reports_invalid_tasksets(gpu):
         B.gcaps_destroy(ctx)
 
 
-def test_captured_call_replays(oracle, gpu):
+def test_captured_call_replays(oracle, route):
     """One device-entry call recorded into a HIP graph (after a warm-up call that made the context's
-    allocations) and replayed, with eager calls of other sizes in between: every replay gives the eager result."""
+    allocations) and replayed, with eager calls of other sizes in between: every replay gives the eager result.  In two
+    launches the list between them and its counters are part of what a replay finds reset."""
     import torch
-    B, _, _ = gpu
-    stream = torch.cuda.Stream()
-    ctx = B.gcaps_create(0, stream.cuda_stream)
-    try:
-        batch, other = relaxed_workload(3_000, seed=51), relaxed_workload(777, seed=52)
-        want_r, want_s, _ = oracle.rta_batch(batch, BOTH, SUSPEND, threads=16)
-        d = B.to_device(batch)
-        N, n = batch["cpu_us"].shape
-        d_resp = torch.empty((2, N, n), dtype=torch.int64, device="cuda:0")
-        d_sched = torch.empty((2, N), dtype=torch.uint8, device="cuda:0")
-        B.gcaps_rta_batch_device(ctx, d, BOTH, SUSPEND, d_resp, d_sched)  # warm-up: allocations happen here
-        B.gcaps_status(ctx)
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=stream):
-            B.gcaps_rta_batch_device(ctx, d, BOTH, SUSPEND, d_resp, d_sched)
-        for k in range(4):
-            d_resp.fill_(-7)
-            d_sched.fill_(9)
-            torch.cuda.synchronize()
-            graph.replay()
-            torch.cuda.synchronize()
-            assert np.array_equal(d_resp.cpu().numpy(), want_r) and np.array_equal(d_sched.cpu().numpy(), want_s), k
-            # eager work of the same context between the replays
-            got = B.gcaps_rta_batch(ctx, other, BOTH, BUSY)
-            ref = oracle.rta_batch(other, BOTH, BUSY, threads=16)
-            assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
-            if k % 2:
-                B.gcaps_gprio_assign_batch(ctx, other, BUSY)
-        B.gcaps_status(ctx)
-    finally:
-        B.gcaps_destroy(ctx)
+    B, ctx, stream = route
+    batch, other = relaxed_workload(3_000, seed=51), relaxed_workload(777, seed=52)
+    want_r, want_s, _ = oracle.rta_batch(batch, BOTH, SUSPEND, threads=16)
+    d = B.to_device(batch)
+    N, n = batch["cpu_us"].shape
+    d_resp = torch.empty((2, N, n), dtype=torch.int64, device="cuda:0")
+    d_sched = torch.empty((2, N), dtype=torch.uint8, device="cuda:0")
+    B.gcaps_rta_batch_device(ctx, d, BOTH, SUSPEND, d_resp, d_sched)  # warm-up: allocations happen here
+    B.gcaps_status(ctx)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        B.gcaps_rta_batch_device(ctx, d, BOTH, SUSPEND, d_resp, d_sched)
+    for k in range(4):
+        d_resp.fill_(-7)
+        d_sched.fill_(9)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(d_resp.cpu().numpy(), want_r) and np.array_equal(d_sched.cpu().numpy(), want_s), k
+        # eager work of the same context between the replays
+        got = B.gcaps_rta_batch(ctx, other, BOTH, BUSY)
+        ref = oracle.rta_batch(other, BOTH, BUSY, threads=16)
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+        if k % 2:
+            B.gcaps_gprio_assign_batch(ctx, other, BUSY)
+    B.gcaps_status(ctx)
 
 
 def test_recorded_call_that_would_have_to_allocate_is_refused(oracle, gpu):
