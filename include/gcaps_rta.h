@@ -435,9 +435,9 @@ int gcaps_set_continue_after_miss(gcaps_ctx *ctx, int enable);
  * instruction, eight wavefronts per SIMD, is timed with events on the context's stream (the call waits for
  * the stream, allocates a few KB of device memory for the duration of the call and frees it).
  *   lane_ops_per_s[k]  lane-operations per second of kind k (a wavefront instruction = 64; multiply-add = 1);
- *                      GCAPS_PROBE_TERM is the four-instruction sequence of one interference term
- *                      ceil((R + J) / T) * cost of the fast kernels (add, mul_hi_u24, shift, mad_u24),
- *                      counted as four lane-operations
+ *                      GCAPS_PROBE_TERM is the three-instruction sequence of one interference term
+ *                      ceil((R + J) / T) * cost of the kernels that walk all ranks (float add, fma, mad_u24),
+ *                      counted as three lane-operations
  *   cu_count, clock_khz, wavefront_size, simd_per_cu   as the HIP runtime reports them for the device
  *   spec_lane_ops_per_s   cu_count * simd_per_cu * 16 lanes * clock: one full-rate 32-bit operation per
  *                      lane and cycle
