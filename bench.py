@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="e6cf53f0fc60f8550874623a8a1efdc7da1b49271630b8dd495b854818d010bc", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=56_954_704, valu_lane_ops=2_598_291_533),
-                            suspend=dict(valu_wave_insts=61_934_984, valu_lane_ops=2_697_817_807)),
-                  "0": dict(busy=dict(valu_wave_insts=355_113_225, valu_lane_ops=20_370_891_972),
-                            suspend=dict(valu_wave_insts=529_786_483, valu_lane_ops=30_351_120_037))})
+    csrc_sha256="d59d7761466836df6c58c0173c95047d760ec7897b2f5d712618e97c9afe79d9", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=56_966_454, valu_lane_ops=2_599_002_849),
+                            suspend=dict(valu_wave_insts=61_956_635, valu_lane_ops=2_699_111_287)),
+                  "0": dict(busy=dict(valu_wave_insts=355_111_084, valu_lane_ops=20_370_765_453),
+                            suspend=dict(valu_wave_insts=529_779_715, valu_lane_ops=30_350_730_360))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="e6cf53f0fc60f8550874623a8a1efdc7da1b49271630b8dd495b854818d010bc",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915840727, write_bytes=328825386)
+MEASURED_TRAFFIC = dict(csrc_sha256="d59d7761466836df6c58c0173c95047d760ec7897b2f5d712618e97c9afe79d9",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915698548, write_bytes=328832758)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="9a7f111d7b9132efd421532c37695c56b655419beb060ecd888e3522a334dcea",
-                              workload=3, tasksets=1_000_000, fetch_bytes=877998749, write_bytes=242012499)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="b410be74a015e08f4b55b94b4bbb8363b718377f29a9287fd6143686048d9f53",
+                              workload=3, tasksets=1_000_000, fetch_bytes=877929268, write_bytes=242012535)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged
@@ -317,7 +317,7 @@ def main():
     # the arithmetic side: the probe's rates are measured now, on this device
     alu = dict(peak=VALU_PEAK_LANE_OPS, peak_by="256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz",
                note="6 integer ops per interference term evaluated by plain iteration (oracle count); "
-                    "peak_measured_term_mix = the add, 24-bit multiply-high, shift, 24-bit multiply-add of one term "
+                    "peak_measured_term_mix = the float add, fma, 24-bit multiply-add of one term "
                     "in independent chains, measured in this run")
     term_mix = None
     if not args.no_probe:
