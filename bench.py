@@ -344,8 +344,8 @@ def main():
                    measured_active_lanes_per_valu_inst=counted["valu_lane_ops"] / counted["valu_wave_insts"],
                    measured_valu_issue_frac=counted["valu_wave_insts"] * 4 / (256 * 4 * 2.4e9 * m["device_ms_per_step"] * 1e-3),
                    measured_note="hardware counters of an earlier run of these kernel sources over the time of "
-                                 "this run; issue fraction = VALU wavefront-instructions x 4 cycles over the "
-                                 "SIMD-cycles of the step")
+                                 "this run; issue fraction = VALU wavefront-instructions x 4 cycles (what multiplies "
+                                 "sustain; additions issue faster, so that 1 is no upper bound) over the SIMD-cycles of the step")
 
     # the host entry point: pack, copy in, analyse, copy out (the PCIe-inclusive rate; never `value`)
     end_to_end = None
