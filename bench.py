@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="d59d7761466836df6c58c0173c95047d760ec7897b2f5d712618e97c9afe79d9", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=56_966_454, valu_lane_ops=2_599_002_849),
-                            suspend=dict(valu_wave_insts=61_956_635, valu_lane_ops=2_699_111_287)),
-                  "0": dict(busy=dict(valu_wave_insts=355_111_084, valu_lane_ops=20_370_765_453),
-                            suspend=dict(valu_wave_insts=529_779_715, valu_lane_ops=30_350_730_360))})
+    csrc_sha256="f3081f2b2c79a713031f1dbe67e98ae4fd5c335f589c62e0400aa0fa6550b1de", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=56_958_993, valu_lane_ops=2_598_554_605),
+                            suspend=dict(valu_wave_insts=61_951_889, valu_lane_ops=2_698_825_778)),
+                  "0": dict(busy=dict(valu_wave_insts=355_111_445, valu_lane_ops=20_370_791_057),
+                            suspend=dict(valu_wave_insts=529_758_975, valu_lane_ops=30_349_539_092))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="d59d7761466836df6c58c0173c95047d760ec7897b2f5d712618e97c9afe79d9",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915698548, write_bytes=328832758)
+MEASURED_TRAFFIC = dict(csrc_sha256="f3081f2b2c79a713031f1dbe67e98ae4fd5c335f589c62e0400aa0fa6550b1de",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915934860, write_bytes=328834480)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="b410be74a015e08f4b55b94b4bbb8363b718377f29a9287fd6143686048d9f53",
-                              workload=3, tasksets=1_000_000, fetch_bytes=877929268, write_bytes=242012535)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="13c317f7a743a2ad6ad365d5f719d4bbfbe59a7ae41c0b02f89891c6a100438e",
+                              workload=3, tasksets=1_000_000, fetch_bytes=878001629, write_bytes=242012659)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged

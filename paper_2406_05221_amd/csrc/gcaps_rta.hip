@@ -416,26 +416,28 @@ bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
 /* One full-depth launch for the whole call instead of two with a list between them.  A small call is bound by latency:
  * the chain of dependent loads of a launch, and a second launch behind it.  A large one is bound by work, most of which
  * the first launch of the two saves where tasksets miss their deadlines within its ranks; it stages no segments of further
- * ranks.  How many do is not known here: the lines lie where a batch that misses at once (periods from 500, overheads of
- * 300, half to nine tenths of every core used; the round-robin pass alone always does) takes as long either way, on
- * inputs that were just analysed and on inputs that were not in any cache.  us in two launches / in one, both
- * policies, self-suspension, such a batch; then a lightly loaded one:
+ * ranks.  How many do is not known here: the lines lie about where a batch that misses at once (periods from 500, overheads
+ * of 300, half to nine tenths of every core used; the round-robin pass alone always does) takes as long either way, some
+ * per cent beyond where a lightly loaded batch gains several times as much.  us in two launches / in one, both policies,
+ * self-suspension, a batch that misses at once; then a lightly loaded one:
  *   6 tasks x 1 segment, 1,000 tasksets 25.9 / 15.4, 28.7 / 16.9; 16,000 27.1 / 20.1, 38.2 / 23.8 (20,000);
- *   16 x 3, 8,000 22.0 / 16.7, 55.4 / 39.0 (9,000); 16,000 22.8 / 19.0, 32,768 24.0 / 25.5;
- *   20 x 3, 8,000 21.2 / 17.5, 66.3 / 48.3 (9,000); 19,660 22.6 / 22.0, cold 26.4 / 28.8;
- *   24 x 3, 8,000 21.6 / 20.2; 24 x 4, 10,922 21.7 / 22.3; 24 x 8, 5,461 22.3 / 25.9 (segments through registers, eight
- *   slots a task: the time to stage them shows from 64 slots a taskset on);
- *   8 x 1 on eight cores, 32,768 16.5 / 21.8; 3 x 1 on three, 12,288 13.6 / 15.1.
- * The round-robin pass alone takes half the time in two launches: 20 x 3, 6,553 14.8 / 14.3, 13,107 15.9 / 17.1.  One or two
- * tasks are settled by the first launch of the two alone: 10.8 / 11.5 with 1,000 tasksets. */
+ *   16 x 3, 8,000 22.0 / 16.7, 55.4 / 39.0 (9,000); 16,000 22.8 / 19.0, 32,768 24.0 / 25.5 (cold 26.7 / 34.1);
+ *   20 x 3, 8,000 21.2 / 17.5, 66.3 / 48.3 (9,000); 19,660 22.6 / 22.0 (cold 26.4 / 28.8), 75.0 / 57.2 (20,000);
+ *   24 x 3, 8,000 21.6 / 20.2; 24 x 4, 8,000 21.1 / 21.1, 16,384 22.1 / 25.2;
+ *   20 x 5, 6,000 21.4 / 20.8; 24 x 8 (segments through registers, eight slots a task), 1,000 20.2 / 22.1, 75.9 / 49.1,
+ *   5,461 22.3 / 25.9, 21,845 25.2 / 37.9;
+ *   8 x 1 on eight cores, 16,384 15.6 / 16.5, 32,768 16.5 / 21.8; 3 x 1 on three, 8,192 13.5 / 14.3, 12,288 13.6 / 15.1.
+ * The passes alone leave less to gain, round-robin least: 20 x 3, 6,553 14.8 / 14.3, 13,107 15.9 / 17.1; 20 x 5, GCAPS alone,
+ * 4,000 17.0 / 18.4.  Up to four tasks are settled by the first launch of the two alone, in 10.8 us for one task and 1,000
+ * tasksets where one launch takes 11.5. */
 bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b, int policy) {
   if (ctx->binning || ctx->screen_tasks != 4u || !quad_all_applies(ctx, b)) return false;
   if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
-  const u32 n = b->n_tasks, cu = (u32)ctx->n_cu;
-  const bool many_slots = b->max_gseg > 3u;
-  if (n < 3u || n > 24u || (many_slots && n * b->max_gseg > 64u)) return false;
-  const u64 tasksets = (u64)b->n_tasksets * (policy == GCAPS_POLICY_RR ? 2u : 1u);
-  return tasksets <= cu * (n <= 5u || many_slots ? 32u : 64u) && tasksets * n <= cu * (many_slots ? 384u : 768u);
+  const u32 n = b->n_tasks, slots = n * b->max_gseg, cu = (u32)ctx->n_cu;
+  const bool both = policy == GCAPS_POLICY_BOTH, rr = policy == GCAPS_POLICY_RR, many = b->max_gseg > 3u;
+  if (n < 3u || n > 24u || (many && slots > (both ? 192u : rr ? 80u : 100u))) return false;
+  const u64 tasksets = (u64)b->n_tasksets * (rr || (many && !both) ? 2u : 1u);
+  return tasksets <= cu * (n <= 4u ? 32u : n <= 8u ? 64u : 96u) && tasksets * n <= cu * (!many ? 1536u : slots <= 100u ? 768u : 384u);
 }
 
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {

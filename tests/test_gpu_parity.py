@@ -410,8 +410,8 @@ def test_calls_in_one_launch_and_in_two(oracle, monkeypatch, shape, tasksets):
         B.gcaps_destroy(ctx)
 
 
-@pytest.mark.parametrize("cores,per_core,S,N", [(1, 2, 1, 1_000), (1, 3, 1, 8_192), (1, 5, 4, 8_192), (2, 3, 3, 16_384), (4, 4, 3, 12_288),
-                                                (4, 4, 4, 6_144), (4, 6, 3, 8_192), (5, 5, 3, 1_000), (4, 5, 4, 1_000)])
+@pytest.mark.parametrize("cores,per_core,S,N", [(1, 2, 1, 1_000), (1, 3, 1, 8_192), (1, 5, 4, 16_384), (2, 3, 3, 16_384), (4, 4, 3, 24_576),
+                                                (4, 5, 3, 19_660), (4, 6, 4, 8_192), (4, 6, 8, 4_096), (4, 5, 5, 9_830), (5, 5, 3, 1_000)])
 def test_default_route_at_its_lines(oracle, gpu, cores, per_core, S, N):
     """The largest call of a shape that takes one launch by default and one taskset more (both policies; round-robin alone
     takes half as many), shapes that never do: the same results."""
