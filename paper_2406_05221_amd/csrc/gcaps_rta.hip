@@ -794,9 +794,9 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
 
 /* The longest schedules first; null (caller order) where there is no memory for the list, for a few tasks (schedules
  * short enough for the sort and the scattered reads behind it to show: 65,536 tasksets of 6 tasks, a horizon of 200,000,
- * 2.49 ms in caller order, 2.72 by length), or where the stream is recording: a recorded simulation uses nothing but the status block, which stays where it is as long as the context
- * lives, so that it can be replayed whatever calls grow the context's buffers afterwards (65,536 tasksets of 20 tasks,
- * a second of task time: 45 ms by length, 54 in caller order). */
+ * 2.49 ms in caller order, 2.72 by length, with the kernel's first form), or where the stream is recording: a recorded
+ * simulation uses nothing but the status block, which stays where it is as long as the context lives, so that it can be
+ * replayed whatever calls grow the context's buffers afterwards. */
 const u32 *simulation_order(gcaps_ctx *ctx, const gcaps_batch *sub, u32 horizon) {
   const u32 N = sub->n_tasksets, blocks = (N + 255u) / 256u;
   if (sub->n_tasks <= sim::kFewTasks || ctx->capturing) return nullptr;
@@ -810,25 +810,25 @@ const u32 *simulation_order(gcaps_ctx *ctx, const gcaps_batch *sub, u32 horizon)
   return order;
 }
 
-/* one launch for all planes: as many workgroups of W lanes per plane as are resident at once; their lanes take further
+/* one launch for all planes: as many workgroups of `lanes` lanes per plane as are resident at once; their lanes take further
  * tasksets as they finish.  The launch prepares the status words of the next call. */
-template <bool BUSY, int W>
+template <bool BUSY, int NG>
 int launch_simulate(gcaps_ctx *ctx, const gcaps_batch *sub, const u32 *offset, const int *gprio, const u32 *order,
-                    int policy, u32 horizon, long long *mort, u32 *jobs, uint8_t *flag, size_t task_stride, size_t ts_stride) {
-  auto fn = sim::simulate_kernel<BUSY, W>;
-  const size_t lds = sim::lds_bytes(sub->n_tasks, W);
+                    int policy, u32 horizon, long long *mort, u32 *jobs, uint8_t *flag, size_t task_stride, size_t ts_stride, u32 lanes) {
+  auto fn = sim::simulate_kernel<BUSY, NG>;
+  const size_t lds = sim::lds_bytes(sub->n_tasks);
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, W, lds) != hipSuccess || per_cu < 1) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, 64, lds) != hipSuccess || per_cu < 1) {
     (void)hipGetLastError();
     per_cu = 1;
   }
   u32 blocks = (u32)ctx->n_cu * (u32)per_cu;
-  const u32 tiles = (sub->n_tasksets + (u32)W - 1u) / (u32)W;
+  const u32 tiles = (sub->n_tasksets + lanes - 1u) / lanes;
   if (blocks > tiles) blocks = tiles;
   if (ctx->sim_blocks_cap && blocks > ctx->sim_blocks_cap) blocks = ctx->sim_blocks_cap;
-  hipLaunchKernelGGL(fn, dim3(blocks, policy == GCAPS_POLICY_BOTH ? 2u : 1u), dim3(W), lds, ctx->stream, *sub, offset,
+  hipLaunchKernelGGL(fn, dim3(blocks, policy == GCAPS_POLICY_BOTH ? 2u : 1u), dim3(64), lds, ctx->stream, *sub, offset,
                      gprio, order, policy, horizon, mort, jobs, flag, task_stride, ts_stride, status_of(ctx), ctx->ts_offset,
-                     ctx->next_status, (u32)fast::kStatusWords);
+                     ctx->next_status, (u32)fast::kStatusWords, lanes);
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -841,28 +841,24 @@ int run_simulate(gcaps_ctx *ctx, const gcaps_batch *b, const uint32_t *d_offset,
     if (begin_chunk(ctx, c0 == 0) != GCAPS_OK) return (int)GCAPS_EDEVICE;
     ctx->wide_only = true;
     const u32 *order = simulation_order(ctx, sub, horizon);
-    auto go = [&](auto busy, auto lanes) {
-      return launch_simulate<decltype(busy)::value, decltype(lanes)::value>(
-          ctx, sub, d_offset ? d_offset + c0 * n : nullptr, d_gprio ? (const int *)(d_gprio + c0 * n) : nullptr, order,
-          policy, horizon, (long long *)(d_mort + c0 * n), d_jobs + c0 * n, d_flag + c0, (size_t)(N * n), (size_t)N);
-    };
-    auto with = [&](auto lanes) {
-      return wait_mode == GCAPS_WAIT_BUSY ? go(std::true_type{}, lanes) : go(std::false_type{}, lanes);
-    };
-    /* Lanes per wavefront: few while that leaves at most 16 wavefronts per CU, for a step takes the longer the more
-     * lanes take part; full half-wavefronts beyond, where the chip is busy (64 lanes: the columns of fewer wavefronts
-     * fit the LDS).  20 tasks, a second, both policies, 4 / 8 / 16 / 32 lanes: 1,000 tasksets 23 / 25 / 30 / 35 ms,
-     * 8,192 23 / 31 / 35 / 37, 16,384 34 / 27 / 33 / 40, 65,536 97 / 66 / 48 / 45 (64: 49).  The columns of few tasks leave
-     * room for all, and their steps differ less from lane to lane: 200,000 tasksets of 3 / 6 / 8 tasks, a horizon of 2,000, 137 / 240 /
-     * 398 us with 64 lanes, 217 / 335 / 461 with 32; 5,000 of 1 / 3 tasks, GCAPS, 20,000, 34 / 91 us with 16 lanes, 46 / 112 with 4. */
-    const u32 nt = sub->n_tasks;
+    /* Lanes per wavefront: 64, but for a few hundred wavefronts of eight lanes where that leaves every one a SIMD of its own (a
+     * turn takes a little longer the more lanes take part).  20 tasks, both policies, 8 / 16 / 32 / 64 lanes: 1,000 tasksets, a second,
+     * 15.9 / 17.6 / 18.4 / 17.4 ms, 100 of them, 100,000, 1.60 / 1.81 / 1.79 / 1.80; 8,192, a second, 18.4 / 19.8 / 18.6 / 18.2, 65,536
+     * 78.2 / 40.6 / 25.5 / 19.4; 3 tasks, GCAPS, 5,000, 20,000, 0.079 / 0.073 / 0.072 / 0.070. */
     const u64 schedules = (u64)sub->n_tasksets * (policy == GCAPS_POLICY_BOTH ? 2u : 1u);
-    const u64 most = (u64)ctx->n_cu * (nt <= sim::kFewTasks / 2u ? 2u : nt <= sim::kFewTasks ? 8u : 16u);
-    if (schedules <= 4u * most) return with(std::integral_constant<int, 4>{});
-    if (schedules <= 8u * most) return with(std::integral_constant<int, 8>{});
-    if (schedules <= 16u * most) return with(std::integral_constant<int, 16>{});
-    if (schedules > 32u * most && nt <= sim::kFewTasks) return with(std::integral_constant<int, 64>{});
-    return with(std::integral_constant<int, 32>{});
+    const u32 lanes = schedules <= (u64)ctx->n_cu * 16u ? 8u : 64u;
+    auto go = [&](auto busy, auto groups) {
+      return launch_simulate<decltype(busy)::value, decltype(groups)::value>(
+          ctx, sub, d_offset ? d_offset + c0 * n : nullptr, d_gprio ? (const int *)(d_gprio + c0 * n) : nullptr, order,
+          policy, horizon, (long long *)(d_mort + c0 * n), d_jobs + c0 * n, d_flag + c0, (size_t)(N * n), (size_t)N, lanes);
+    };
+    auto with = [&](auto groups) {
+      return wait_mode == GCAPS_WAIT_BUSY ? go(std::true_type{}, groups) : go(std::false_type{}, groups);
+    };
+    const u32 nt = sub->n_tasks;
+    return nt <= 8u    ? with(std::integral_constant<int, 2>{})
+           : nt <= 20u ? with(std::integral_constant<int, 5>{})
+                       : with(std::integral_constant<int, 8>{});
   });
 }
 

@@ -410,6 +410,39 @@ def test_recorded_simulation_outlives_larger_calls(oracle, monkeypatch):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("cores,per_core", [(1, 1), (1, 4), (5, 1), (2, 4), (3, 3), (1, 19), (4, 5), (7, 3), (31, 1), (4, 8)])
+def test_group_edges_and_lengths_out_of_the_ordinary(oracle, cores, per_core):
+    """Groups of four tasks that are full, begun and last; eight lanes per wavefront and 64; lengths of zero (a phase
+    that ends in a pass of its own), G^m of zero behind a CPU segment, updates that take no time, equal priorities,
+    and values whose share per CPU segment, stretch on the CPU or next release does not fit the words they are kept in."""
+    import torch
+    from paper_2406_05221_amd import binding as B, taskgen
+    n, horizon = cores * per_core, 700
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        for N in (300, 4200):
+            print(f"{N} tasksets of {n}", flush=True)
+            rng = np.random.default_rng(1000 * n + N)
+            batch = taskgen.generate(N, n_cores=cores, tasks_per_core=per_core, max_gseg=3, util=(0.1, 0.8), eta=(0, 3),
+                                     share=(0.1, 0.5), period=(30, 300), overhead=(0, 3), slice_us=8, seed=N, stream=53)
+            batch = {k: v.copy() for k, v in batch.items()}
+            for name, share in (("cpu_us", 0.1), ("gm_us", 0.25), ("ge_us", 0.15)):
+                batch[name][rng.random(batch[name].shape) < share] = 0
+            batch["prio"][::5] //= 2
+            batch["eps_us"][1::4] = 0
+            huge = rng.random((N, n)) < 0.02
+            batch["cpu_us"][huge] = rng.integers(1 << 24, 1 << 32, (N, n))[huge]
+            batch["period_us"][huge] = 0xFFFFFFFF - rng.integers(0, 40, (N, n))[huge].astype(np.uint32)
+            off = rng.integers(0, 90, (N, n)).astype(np.uint32)
+            off[::3] = 0
+            for wait, policy, offset in ((BUSY, BOTH, off), (SUSPEND, BOTH, None)):
+                want = oracle.simulate_batch(batch, policy, wait, horizon, offset=offset, threads=16)
+                got = B.gcaps_simulate_batch(ctx, batch, policy, wait, horizon, offset=offset)
+                assert all((g == w).all() for g, w in zip(got, want)), (N, wait)
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_bench_size_on_sampled_tasksets(oracle, gpu):
     """The batch size and launch configuration that bench.py times (262,144 tasksets of its recipe: more than
     the lanes that are resident at once), over a tenth of a second of task time; the oracle follows a sample spread over
