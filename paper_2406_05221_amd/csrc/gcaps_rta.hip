@@ -167,6 +167,8 @@ struct gcaps_ctx {
 
 namespace {
 
+constexpr u32 kSmallTasks = 24; /* most tasks of a call in one launch (see one_launch_applies) */
+
 u32 *status_of(const gcaps_ctx *ctx) {
   return (u32 *)ctx->pool.status.ptr + (size_t)ctx->status_block * fast::kStatusWords;
 }
@@ -205,10 +207,10 @@ u32 wide_slots(const gcaps_ctx *ctx, u32 n_tasksets) {
 }
 
 /* the per-lane scratch columns of the one-lane-per-taskset kernels, for `slots` lanes */
+size_t wide_column_bytes(u32 n_tasks, u32 slots) { return (size_t)slots * n_tasks * (4 * sizeof(u32) + 3 * sizeof(u64)); }
 int wide_columns(gcaps_ctx *ctx, u32 n_tasks, u32 slots, wide::Scratch *ws) {
   const size_t col = (size_t)slots * n_tasks;
-  const size_t bytes = col * (4 * sizeof(u32) + 3 * sizeof(u64));
-  int rc = ctx->pool.wide_scratch.reserve(bytes, !ctx->capturing);
+  int rc = ctx->pool.wide_scratch.reserve(wide_column_bytes(n_tasks, slots), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
   char *base = (char *)ctx->pool.wide_scratch.ptr;
   ws->CGm = (u64 *)base;
@@ -370,7 +372,7 @@ int launch_quad(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_res
   if (blocks > max_tiles) blocks = max_tiles;
   hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, ALL>), dim3(blocks), dim3(64), lds, ctx->stream, *b,
                      policy, (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
-                     ctx->resp_stride, ctx->sched_stride, ctx->ts_offset, ctx->cont != 0);
+                     ctx->resp_stride, ctx->sched_stride, ctx->ts_offset, ctx->cont != 0, wide::Scratch{}, (u32 *)nullptr);
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -408,36 +410,68 @@ int launch_quad_all(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_m
 #undef GCAPS_QUAD_S
 }
 
+/* A small call: the register form over every taskset, a wavefront per policy, Q lanes per taskset.  `ws` with columns for
+ * every taskset: nothing is launched behind it. */
+template <bool BUSY, int NSMAX, int SEGS, int Q>
+int launch_small(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_resp, uint8_t *d_sched, const wide::Scratch &ws) {
+  const u32 n = b->n_tasks, N = b->n_tasksets, ts = 64u / (u32)Q;
+  const fast::ListSpec dl{nullptr, nullptr, 1u, N, nullptr, nullptr, nullptr};
+  hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, true, Q, 2>), dim3((N + ts - 1u) / ts), dim3(128),
+                     fast::quad_lds_bytes(n, (u32)Q, 2u), ctx->stream, *b, policy, (long long *)d_resp, d_sched,
+                     status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, 0u, ctx->resp_stride, ctx->sched_stride,
+                     ctx->ts_offset, false, ws, ctx->next_status);
+  return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
+}
+
+/* Lanes per taskset: the more, the fewer terms a lane sums and the fewer tasksets walk in lock step, but the more
+ * wavefronts.  Sixteen while those are at most about two per SIMD, eight up to nine wavefronts per CU.  us with
+ * 4 / 8 / 16 lanes, both policies, self-suspension: 6 tasks, 1,000 tasksets 9.9 / 9.5 / 9.2, 8,000 11.3 / 10.8 / 12.3; 16 tasks x 3
+ * segments, lightly loaded, 3,000 20.2 / 18.1 / 17.1, 9,000 21.2 / 23.6 / 35.6 (overloaded 13.9 / 12.6 / 14.0, mixed 24.1 / 24.9 /
+ * 35.5); 20 x 3, 770 25.4 / 22.1 / 19.8, 9,000 26.7 / 29.7 / 42.2 (13.6 / 12.2 / 12.7, 31.4 / 30.4 / 43.9), 19,000
+ * 36.8 / 49.3 / 65.7; 24 x 3, 3,000 30.6 / 26.9 / 24.2, 8,000 32.1 / 29.0 / 35.0. */
+int launch_small_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp, uint8_t *d_sched,
+                     const wide::Scratch &ws) {
+  const bool busy = wait_mode == GCAPS_WAIT_BUSY;
+  const u32 n = b->n_tasks, N = b->n_tasksets, cu = (u32)ctx->n_cu;
+#define GCAPS_SMALL_S(NS, SEGS, Q)                                                \
+  (busy ? launch_small<true, NS, SEGS, Q>(ctx, b, policy, d_resp, d_sched, ws) \
+        : launch_small<false, NS, SEGS, Q>(ctx, b, policy, d_resp, d_sched, ws))
+#define GCAPS_SMALL(NS, Q) (b->max_gseg <= 3 ? GCAPS_SMALL_S(NS, 3, Q) : GCAPS_SMALL_S(NS, fast::kPrefetchSegs, Q))
+  if (N <= 16u * cu) return n <= 16 ? GCAPS_SMALL(1, 16) : GCAPS_SMALL(2, 16);
+  if (N <= 36u * cu) return n <= 16 ? GCAPS_SMALL(2, 8) : GCAPS_SMALL(3, 8);
+  return n <= 20 ? GCAPS_SMALL(5, 4) : GCAPS_SMALL(6, 4);
+#undef GCAPS_SMALL
+#undef GCAPS_SMALL_S
+}
+
 bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
   return ctx->deep_lanes == 4 && b->n_tasks <= fast::kQuadMaxTasks && b->max_gseg <= (u32)fast::kPrefetchSegs &&
          !ctx->legacy_deep;
 }
 
-/* One full-depth launch for the whole call instead of two with a list between them.  A small call is bound by latency:
- * the chain of dependent loads of a launch, and a second launch behind it.  A large one is bound by work, most of which
- * the first launch of the two saves where tasksets miss their deadlines within its ranks; it stages no segments of further
- * ranks.  How many do is not known here: the lines lie about where a batch that misses at once (periods from 500, overheads
- * of 300, half to nine tenths of every core used; the round-robin pass alone always does) takes as long either way, some
- * per cent beyond where a lightly loaded batch gains several times as much.  us in two launches / in one, both policies,
- * self-suspension, a batch that misses at once; then a lightly loaded one:
- *   6 tasks x 1 segment, 1,000 tasksets 25.9 / 15.4, 28.7 / 16.9; 16,000 27.1 / 20.1, 38.2 / 23.8 (20,000);
- *   16 x 3, 8,000 22.0 / 16.7, 55.4 / 39.0 (9,000); 16,000 22.8 / 19.0, 32,768 24.0 / 25.5 (cold 26.7 / 34.1);
- *   20 x 3, 8,000 21.2 / 17.5, 66.3 / 48.3 (9,000); 19,660 22.6 / 22.0 (cold 26.4 / 28.8), 75.0 / 57.2 (20,000);
- *   24 x 3, 8,000 21.6 / 20.2; 24 x 4, 8,000 21.1 / 21.1, 16,384 22.1 / 25.2;
- *   20 x 5, 6,000 21.4 / 20.8; 24 x 8 (segments through registers, eight slots a task), 1,000 20.2 / 22.1, 75.9 / 49.1,
- *   5,461 22.3 / 25.9, 21,845 25.2 / 37.9;
- *   8 x 1 on eight cores, 16,384 15.6 / 16.5, 32,768 16.5 / 21.8; 3 x 1 on three, 8,192 13.5 / 14.3, 12,288 13.6 / 15.1.
- * The passes alone leave less to gain, round-robin least: 20 x 3, 6,553 14.8 / 14.3, 13,107 15.9 / 17.1; 20 x 5, GCAPS alone,
- * 4,000 17.0 / 18.4.  Up to four tasks are settled by the first launch of the two alone, in 10.8 us for one task and 1,000
- * tasksets where one launch takes 11.5. */
+/* One full-depth launch for the whole call instead of two with a list between them and a third behind.  A small call is
+ * bound by latency: the chain of dependent loads of a launch, and the launches behind it.  A large one is bound by work,
+ * most of which the first launch of the two saves where tasksets miss their deadlines within its ranks; it stages no segments
+ * of further ranks.  How many do is not known here: the lines lie below where a batch that misses at once (periods from
+ * 500, overheads of 300, half to nine tenths of every core used; the round-robin pass alone always does) or one of mixed
+ * load takes as long either way.  us in two launches / in one, both policies, self-suspension, a batch that misses at once; then
+ * a mixed one:
+ *   1 task, 16,384 tasksets 15.3 / 10.0, 13.4 / 9.7, 32,768 13.6 / 12.1; 2 tasks, 24,576 14.4 / 9.7, 32,768 14.5 / 13.4;
+ *   6 x 1 segment, 8,000 32.4 / 11.7, 31.7 / 10.9; 49,152 38.6 / 27.1, 49.9 / 26.8; 98,304 43.4 / 47.9;
+ *   20 x 3, 8,000 30.4 / 12.2, 62.7 / 30.4; 49,152 36.8 / 28.6, 88.0 / 82.1; 65,536 38.1 / 33.0, 99.6 / 101.7;
+ *   24 x 4, 32,768 32.1 / 24.1, 84.2 / 83.9; 49,152 34.4 / 30.7, 100.0 / 106.0;
+ *   20 x 5, 49,152 45.1 / 37.6, 106.6 / 91.1; 24 x 8, 24,576 34.2 / 30.4, 106.4 / 65.6; 32,768 36.4 / 43.1.
+ * Round-robin alone, a batch that misses at once: 20 x 3, 16,384 18.2 / 10.4, 32,768 19.2 / 18.7; 24 x 4, 16,384 20.6 / 12.7,
+ * 32,768 21.2 / 22.4; 20 x 5, 16,384 16.3 / 14.0, 32,768 18.0 / 25.9; 24 x 8, 16,384 18.7 / 22.1. */
 bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b, int policy) {
   if (ctx->binning || ctx->screen_tasks != 4u || !quad_all_applies(ctx, b)) return false;
   if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
-  const u32 n = b->n_tasks, slots = n * b->max_gseg, cu = (u32)ctx->n_cu;
-  const bool both = policy == GCAPS_POLICY_BOTH, rr = policy == GCAPS_POLICY_RR, many = b->max_gseg > 3u;
-  if (n < 3u || n > 24u || (many && slots > (both ? 192u : rr ? 80u : 100u))) return false;
-  const u64 tasksets = (u64)b->n_tasksets * (rr || (many && !both) ? 2u : 1u);
-  return tasksets <= cu * (n <= 4u ? 32u : n <= 8u ? 64u : 96u) && tasksets * n <= cu * (!many ? 1536u : slots <= 100u ? 768u : 384u);
+  const u32 n = b->n_tasks, S = b->max_gseg;
+  if (n > kSmallTasks) return false;
+  const bool rr = policy == GCAPS_POLICY_RR, large = S > 4u && n * S > 100u;
+  u32 per_cu = large ? (rr ? 32u : 96u) : S > 4u ? (rr ? 64u : 192u) : S == 4u ? (rr ? 80u : 128u) : rr ? 96u : 192u;
+  if (n <= 4u && per_cu > 64u) per_cu = 64u;
+  return b->n_tasksets <= (u32)ctx->n_cu * per_cu;
 }
 
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
@@ -482,12 +516,23 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
   if (ctx->cont) /* the full-depth launch alone */
     ctx->wide_only = n > fast::kMaxTasks || fast::deep_lds_bytes(n, ctx->deep_lanes) > (size_t)ctx->lds_limit;
   if (ctx->wide_only) return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, nullptr, nullptr, N);
+  const bool one = !ctx->cont && one_launch_applies(ctx, b, policy);
+  if (one && n <= kSmallTasks && wide_slots(ctx, N) >= N &&
+      ctx->pool.wide_scratch.bytes >= wide_column_bytes(n, wide_slots(ctx, N))) {
+    /* With a column for every taskset what is outside the fast range is redone where it is found.  Columns that are not there yet
+     * are allocated by a launch over a list behind this one, while this one runs (a context's first call of 9,000 tasksets of 16
+     * tasks: 45 us, 54 with the allocation in front of the only launch). */
+    wide::Scratch ws;
+    const int rc = wide_columns(ctx, n, wide_slots(ctx, N), &ws);
+    return rc != GCAPS_OK ? rc : launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws);
+  }
   int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
 
-  if (ctx->cont || one_launch_applies(ctx, b, policy)) {
+  if (ctx->cont || one) {
     /* continue-after-miss: nothing is settled early, the full-depth launch takes every taskset */
-    rc = quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
+    rc = one && n <= kSmallTasks ? launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, wide::Scratch{})
+         : quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
                                   : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
     if (rc != GCAPS_OK) return rc;
     const u32 *count = (const u32 *)status_of(ctx) + fast::ST_WIDE_COUNT;

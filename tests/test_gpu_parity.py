@@ -410,6 +410,33 @@ def test_calls_in_one_launch_and_in_two(oracle, monkeypatch, shape, tasksets):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("cores,per_core,S", [(1, 1, 1), (1, 3, 8), (4, 4, 3), (1, 17, 4), (4, 5, 0), (3, 7, 3), (4, 6, 8)])
+@pytest.mark.parametrize("N", [1, 3, 5, 4_096, 4_097, 9_217])
+def test_small_calls_by_lanes_per_taskset(oracle, gpu, cores, per_core, S, N):
+    """A small call gives a taskset sixteen, eight or four lanes by its size (256 compute units: up to 4,096 and up to 9,216
+    tasksets), a wavefront per policy; term registers for up to 16, 20 and 24 tasks; tasksets outside the 24-bit range
+    are redone where they are found, the first and the last of a tile among them, and are counted."""
+    B, ctx, _ = gpu
+    batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
+    rng = np.random.default_rng(N)
+    odd = np.unique(np.concatenate([[0, N - 1], rng.integers(0, N, N // 40)]))
+    batch["cpu_us"][odd, 0] = 2**23
+    batch["period_us"][odd, 0] = 2**25
+    batch["deadline_us"][odd, 0] = 2**25
+    batch["prio"][odd, 0] = batch["prio"][odd].min(axis=1) - 1  # analysed last, if at all
+    batch["prio"][odd[::2], 0] += 1_000  # or first
+    for policy in (BOTH, RR, GCAPS):
+        compare(oracle, B, ctx, batch, policy)
+    count = B.gcaps_last_wide_count(ctx)
+    assert (0 < count <= odd.size), (count, odd.size)
+    bad = {k: v.copy() for k, v in batch.items()}
+    bad["period_us"][N // 2, 0] = 0
+    with pytest.raises(B.GcapsError) as e:
+        B.gcaps_rta_batch(ctx, bad, BOTH, SUSPEND)
+    assert e.value.first_bad == N // 2
+    compare(oracle, B, ctx, batch)
+
+
 @pytest.mark.parametrize("cores,per_core,S,N", [(1, 2, 1, 1_000), (1, 3, 1, 8_192), (1, 5, 4, 16_384), (2, 3, 3, 16_384), (4, 4, 3, 24_576),
                                                 (4, 5, 3, 19_660), (4, 6, 4, 8_192), (4, 6, 8, 4_096), (4, 5, 5, 9_830), (5, 5, 3, 1_000)])
 def test_default_route_at_its_lines(oracle, gpu, cores, per_core, S, N):
