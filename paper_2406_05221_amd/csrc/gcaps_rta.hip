@@ -419,7 +419,7 @@ int launch_small(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_re
   hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, true, Q, 2>), dim3((N + ts - 1u) / ts), dim3(128),
                      fast::quad_lds_bytes(n, (u32)Q, 2u), ctx->stream, *b, policy, (long long *)d_resp, d_sched,
                      status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, 0u, ctx->resp_stride, ctx->sched_stride,
-                     ctx->ts_offset, false, ws, ctx->next_status);
+                     ctx->ts_offset, ctx->cont != 0, ws, ctx->next_status);
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -442,6 +442,35 @@ int launch_small_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_
   return n <= 20 ? GCAPS_SMALL(5, 4) : GCAPS_SMALL(6, 4);
 #undef GCAPS_SMALL
 #undef GCAPS_SMALL_S
+}
+
+/* Lanes per taskset of the two kernels of Sec. 5.4.  More of them shorten the chain of a taskset and put fewer tasksets in
+ * lock step; fewer do less work alike in every lane of a taskset.  Above 20 tasks eight lanes are the better ones at every size: four
+ * need eight term registers each, which leave room for three wavefronts per SIMD.  us with 4 (four lanes: and a launch over the
+ * list behind) / 8 / 16 lanes, self-suspension, lightly loaded (overloaded), three segments:
+ *   search: 6 tasks, 4,096 tasksets 14.4 / 10.4 / 10.3, 24,576 16.5 / 12.0 / 12.1, 98,304 32.3 / 30.3, 200,000 48.9 / 49.8;
+ *   16, 6,000 38.6 / 25.0 / 22.6, 9,216 busy 35.3 / 24.5 / 25.0, 98,304 98 / 86 (50 / 45), 600,000 398 / 390 (140 / 156);
+ *   20, 6,000 49.2 / 36.4 / 33.0, 24,576 62 / 50 / 55, 49,152 75 / 78 (45 / 37), 600,000 515 / 563 (159 / 174);
+ *   24, 6,000 72.7 / 44.6 / 37.8, 600,000 908 / 671 (241 / 173); 32, 6,000 98.8 / 68.3 / 55.1, 600,000 1,374 / 1,061 (290 / 225).
+ *   given: 6 tasks, 2,000 14.6 / 9.5 / 9.7, 4,096 15.2 / 10.6 / 12.2, 16,384 19.5 / 18.7 / 27.1, 24,576 23.6 / 23.5;
+ *   16, 4,096 28.1 / 18.9 / 18.1, 24,576 41.0 / 34.8 / 48.5, 200,000 158 / 152 (137 / 152); 20, 4,096 34.0 / 25.4 / 24.0,
+ *   24,576 49.5 / 44.6 / 57.9, 49,152 71 / 74 (67 / 65), 200,000 201 / 221; 24, 200,000 346 / 261 (254 / 195);
+ *   32, 4,096 66.9 / 44.5 / 33.5, 200,000 520 / 424 (354 / 291). */
+u32 search_lanes(const gcaps_ctx *ctx, u32 n, u32 N) {
+  const u32 cu = (u32)ctx->n_cu;
+  if (N <= 24u * cu) return 16u;
+  return n > 20 || N <= (n <= 16 ? 384u : 96u) * cu ? 8u : 4u;
+}
+u32 given_lanes(const gcaps_ctx *ctx, u32 n, u32 N) {
+  const u32 cu = (u32)ctx->n_cu;
+  if (N <= (n <= 12 ? 12u : 16u) * cu) return 16u;
+  return n > 20 || N <= (n <= 8 ? 64u : 96u) * cu ? 8u : 4u;
+}
+
+/* columns of the 64-bit kernels for every taskset of a call, if they are there already */
+bool columns_at_hand(gcaps_ctx *ctx, u32 n, u32 N, wide::Scratch *ws) {
+  const u32 slots = wide_slots(ctx, N);
+  return slots >= N && ctx->pool.wide_scratch.bytes >= wide_column_bytes(n, slots) && wide_columns(ctx, n, slots, ws) == GCAPS_OK;
 }
 
 bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
@@ -472,6 +501,16 @@ bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b, int policy) 
   u32 per_cu = large ? (rr ? 32u : 96u) : S > 4u ? (rr ? 64u : 192u) : S == 4u ? (rr ? 80u : 128u) : rr ? 96u : 192u;
   if (n <= 4u && per_cu > 64u) per_cu = 64u;
   return b->n_tasksets <= (u32)ctx->n_cu * per_cu;
+}
+
+/* Continue-after-miss in the small form (every task is analysed either way).  us in the persistent form with a launch over
+ * the list behind / in the small one, both policies (round-robin alone), busy-waiting, lightly loaded: 6 tasks x 3 segments, 4,096 tasksets
+ * 17.5 / 10.7, 24,576 24.4 / 13.6; 20 x 3, 4,096 39.8 / 22.1, 24,576 53.9 / 34.4 (33.3 / 24.6); 24 x 3, 24,576 64.4 / 42.1, 32,768
+ * 68.2 / 64.5 (42.3 / 48.6); 24 x 8, 24,576 79.4 / 58.9 (53.7 / 44.1); 20 x 5, 32,768 62.0 / 59.9 (42.0 / 48.9). */
+bool continue_small(const gcaps_ctx *ctx, const gcaps_batch *b) {
+  if (!quad_all_applies(ctx, b) || b->n_tasks > kSmallTasks) return false;
+  if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
+  return b->n_tasksets <= (u32)ctx->n_cu * 96u;
 }
 
 bool quad_applies(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
@@ -516,22 +555,20 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
   if (ctx->cont) /* the full-depth launch alone */
     ctx->wide_only = n > fast::kMaxTasks || fast::deep_lds_bytes(n, ctx->deep_lanes) > (size_t)ctx->lds_limit;
   if (ctx->wide_only) return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, nullptr, nullptr, N);
-  const bool one = !ctx->cont && one_launch_applies(ctx, b, policy);
-  if (one && n <= kSmallTasks && wide_slots(ctx, N) >= N &&
-      ctx->pool.wide_scratch.bytes >= wide_column_bytes(n, wide_slots(ctx, N))) {
+  const bool one = ctx->cont ? continue_small(ctx, b) : one_launch_applies(ctx, b, policy);
+  wide::Scratch ws{};
+  if (one && n <= kSmallTasks && columns_at_hand(ctx, n, N, &ws)) {
     /* With a column for every taskset what is outside the fast range is redone where it is found.  Columns that are not there yet
      * are allocated by a launch over a list behind this one, while this one runs (a context's first call of 9,000 tasksets of 16
      * tasks: 45 us, 54 with the allocation in front of the only launch). */
-    wide::Scratch ws;
-    const int rc = wide_columns(ctx, n, wide_slots(ctx, N), &ws);
-    return rc != GCAPS_OK ? rc : launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws);
+    return launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws);
   }
   int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
 
   if (ctx->cont || one) {
     /* continue-after-miss: nothing is settled early, the full-depth launch takes every taskset */
-    rc = one && n <= kSmallTasks ? launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, wide::Scratch{})
+    rc = one && n <= kSmallTasks ? launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws)
          : quad_all_applies(ctx, b) ? launch_quad_all(ctx, b, policy, wait_mode, d_resp, d_sched)
                                   : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
     if (rc != GCAPS_OK) return rc;
@@ -692,25 +729,34 @@ int run_gprio_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const u
   if (!ctx->wide_only && !ctx->gprio_list) {
     /* one pass: a wavefront per tile of consecutive tasksets reads them once, settles or searches them, and
      * writes their outputs */
-    int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
+    const u32 lanes = search_lanes(ctx, n, N);
+    wide::Scratch own{};
+    const bool alone = lanes > 4u && columns_at_hand(ctx, n, N, &own);
+    int rc = alone ? GCAPS_OK : ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
     if (rc != GCAPS_OK) return rc;
     u32 *wl = (u32 *)ctx->pool.wide_list.ptr;
     const bool busy = wait_mode == GCAPS_WAIT_BUSY;
-    /* sixteen tasksets per wavefront: wider tiles (32, 64) fill the quads of the search better but hold fewer
-     * wavefronts per compute unit, and measured slower on every workload */
-    constexpr u32 tw = 16;
+    /* sixteen tasksets per wavefront of a large call: wider tiles (32, 64) fill the quads of the search better but hold
+     * fewer wavefronts per compute unit, and measured slower on every workload */
+    const u32 tw = 64u / lanes;
     const size_t lds = gprio::tile_lds_bytes(n, tw);
     const dim3 grid((N + tw - 1u) / tw), block(64);
-#define GCAPS_GPRIO_TILE(BUSY, NS)                                                                       \
-  hipLaunchKernelGGL((gprio::gprio_tile_kernel<BUSY, NS, 16>), grid, block, lds, ctx->stream, *b, d_skip, \
-                     (int *)d_gprio, (long long *)d_resp, d_sched, status, wl, ctx->ts_offset)
-    if (n <= 20) {
-      if (busy) GCAPS_GPRIO_TILE(true, 5); else GCAPS_GPRIO_TILE(false, 5);
+#define GCAPS_GPRIO_TILE_W(BUSY, NS, Q)                                                                    \
+  hipLaunchKernelGGL((gprio::gprio_tile_kernel<BUSY, NS, Q>), grid, block, lds, ctx->stream, *b, d_skip,   \
+                     (int *)d_gprio, (long long *)d_resp, d_sched, status, wl, ctx->ts_offset, own, ctx->next_status)
+#define GCAPS_GPRIO_TILE(NS, Q) \
+  do { if (busy) GCAPS_GPRIO_TILE_W(true, NS, Q); else GCAPS_GPRIO_TILE_W(false, NS, Q); } while (0)
+    if (lanes == 16u) {
+      if (n <= 16) GCAPS_GPRIO_TILE(1, 16); else GCAPS_GPRIO_TILE(2, 16);
+    } else if (lanes == 8u) {
+      if (n <= 16) GCAPS_GPRIO_TILE(2, 8); else if (n <= 24) GCAPS_GPRIO_TILE(3, 8); else GCAPS_GPRIO_TILE(4, 8);
     } else {
-      if (busy) GCAPS_GPRIO_TILE(true, 8); else GCAPS_GPRIO_TILE(false, 8);
+      GCAPS_GPRIO_TILE(5, 4);
     }
 #undef GCAPS_GPRIO_TILE
+#undef GCAPS_GPRIO_TILE_W
     if (hipGetLastError() != hipSuccess) return GCAPS_EDEVICE;
+    if (alone) return GCAPS_OK;
     d_list = wl;
     d_count = status + fast::ST_WIDE_COUNT;
     items = N < 65536u ? N : 65536u;
@@ -789,39 +835,47 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
     const int *gp = (const int *)(d_gprio + c0 * n);
     long long *resp = (long long *)(d_resp + c0 * n);
     u32 *status = status_of(ctx);
-    const size_t lds = gprio::given_lds_bytes(sub->n_tasks);
-    ctx->wide_only = sub->n_tasks > 32 || lds > (size_t)ctx->lds_limit;
+    const u32 nt = sub->n_tasks;
+    ctx->wide_only = nt > 32 || gprio::given_lds_bytes(nt, 4u) > (size_t)ctx->lds_limit;
     const u32 *d_list = nullptr, *d_count = nullptr;
     u32 items = N;
     if (!ctx->wide_only) {
-      int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
+      const u32 lanes = given_lanes(ctx, nt, N);
+      wide::Scratch own{};
+      const bool alone = lanes > 4u && columns_at_hand(ctx, nt, N, &own);
+      int rc = alone ? GCAPS_OK : ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
       if (rc != GCAPS_OK) return rc;
-      const bool busy = wait_mode == GCAPS_WAIT_BUSY;
-      const bool small = sub->n_tasks <= 20;
-      const void *fn = small ? (busy ? (const void *)gprio::gprio_given_fast_kernel<true, 5>
-                                     : (const void *)gprio::gprio_given_fast_kernel<false, 5>)
-                             : (busy ? (const void *)gprio::gprio_given_fast_kernel<true, 8>
-                                     : (const void *)gprio::gprio_given_fast_kernel<false, 8>);
-      int per_cu = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64, lds) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        per_cu = 1;
-      }
-      u32 blocks = (u32)ctx->n_cu * (u32)per_cu;
-      const u32 tiles = (N + 15u) / 16u;
-      if (blocks > tiles) blocks = tiles;
-      const dim3 grid(blocks), block(64);
       u32 *wl = (u32 *)ctx->pool.wide_list.ptr;
-#define GCAPS_GIVEN_LAUNCH(BUSY, NS)                                                                            \
-  hipLaunchKernelGGL((gprio::gprio_given_fast_kernel<BUSY, NS>), grid, block, lds, ctx->stream, *sub, gp, resp, \
-                     d_sched + c0, status, wl, ctx->ts_offset)
-      if (small) {
-        if (busy) GCAPS_GIVEN_LAUNCH(true, 5); else GCAPS_GIVEN_LAUNCH(false, 5);
+      auto launch = [&](auto busy, auto ns, auto q) {
+        constexpr int Q = decltype(q)::value;
+        auto fn = gprio::gprio_given_fast_kernel<decltype(busy)::value, decltype(ns)::value, Q>;
+        const size_t lds = gprio::given_lds_bytes(nt, (u32)Q);
+        u32 blocks = (N * (u32)Q + 63u) / 64u; /* tiles */
+        if constexpr (Q == 4) { /* persistent: as many workgroups as are resident at once */
+          int per_cu = 0;
+          if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, 64, lds) != hipSuccess || per_cu < 1) {
+            (void)hipGetLastError();
+            per_cu = 1;
+          }
+          blocks = std::min(blocks, (u32)ctx->n_cu * (u32)per_cu);
+        }
+        hipLaunchKernelGGL(fn, dim3(blocks), dim3(64), lds, ctx->stream, *sub, gp, resp, d_sched + c0, status, wl,
+                           ctx->ts_offset, own, ctx->next_status);
+      };
+      auto with = [&](auto ns, auto q) {
+        if (wait_mode == GCAPS_WAIT_BUSY) launch(std::true_type{}, ns, q); else launch(std::false_type{}, ns, q);
+      };
+#define GCAPS_GIVEN(NS, Q) with(std::integral_constant<int, NS>{}, std::integral_constant<int, Q>{})
+      if (lanes == 16u) {
+        if (nt <= 16) GCAPS_GIVEN(1, 16); else GCAPS_GIVEN(2, 16);
+      } else if (lanes == 8u) {
+        if (nt <= 16) GCAPS_GIVEN(2, 8); else if (nt <= 24) GCAPS_GIVEN(3, 8); else GCAPS_GIVEN(4, 8);
       } else {
-        if (busy) GCAPS_GIVEN_LAUNCH(true, 8); else GCAPS_GIVEN_LAUNCH(false, 8);
+        GCAPS_GIVEN(5, 4);
       }
-#undef GCAPS_GIVEN_LAUNCH
+#undef GCAPS_GIVEN
       if (hipGetLastError() != hipSuccess) return (int)GCAPS_EDEVICE;
+      if (alone) return (int)GCAPS_OK;
       d_list = wl;
       d_count = status + fast::ST_WIDE_COUNT;
       items = N < 65536u ? N : 65536u;

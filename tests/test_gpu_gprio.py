@@ -271,6 +271,54 @@ def admissible_levels(batch, rng):
     return levels
 
 
+@pytest.mark.parametrize("cores,per_core,S", [(1, 1, 1), (2, 4, 3), (3, 3, 8), (4, 4, 3), (1, 17, 3), (4, 5, 0), (3, 7, 3), (4, 6, 5),
+                                              (1, 25, 2), (4, 8, 9)])
+@pytest.mark.parametrize("N", [1, 3, 5, 4_097, 6_145, 24_577])
+def test_lanes_per_taskset(oracle, gpu, cores, per_core, S, N):
+    """The search and the analysis for given priorities give a taskset sixteen, eight or four lanes by the numbers of tasksets and of tasks
+    (256 compute units: lines at 3,072, 4,096, 6,144, 16,384 and 24,576 tasksets, at 8, 12, 16, 20 and 24 tasks); those outside the
+    24-bit range are redone where they are found, the first and the last of a tile among them, and are counted."""
+    B, ctx, _ = gpu
+    n = cores * per_core
+    batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
+    rng = np.random.default_rng(N + n)
+    odd = np.unique(np.concatenate([[0, N - 1], rng.integers(0, N, N // 40)]))
+    batch["cpu_us"][odd, 0] = 2**23
+    batch["period_us"][odd, 0] = 2**25
+    batch["deadline_us"][odd, 0] = 2**25
+    skip = (rng.random(N) < 0.3).astype(np.uint8)
+    skip[odd] = 0
+    for _ in range(2):  # the second call finds columns for every taskset
+        compare(oracle, B, ctx, batch, skip)
+        assert B.gcaps_last_wide_count(ctx) == odd.size
+    shift = rng.integers(-n, n + 1, size=(N, cores)).astype(np.int32)
+    gprio = np.ascontiguousarray(batch["prio"] + np.take_along_axis(shift, batch["core"].astype(np.int64), axis=1))
+    for wait in (BUSY, SUSPEND):
+        want_r, want_s = oracle.gprio_rta_batch(batch, gprio, wait)
+        got_r, got_s = B.gcaps_gprio_rta_batch(ctx, batch, wait, gprio)
+        assert (got_r == want_r).all() and (got_s == want_s).all()
+        assert B.gcaps_last_wide_count(ctx) >= odd.size
+    bad = {k: v.copy() for k, v in batch.items()}
+    bad["period_us"][N // 2, 0] = 0
+    for call in (lambda: B.gcaps_gprio_assign_batch(ctx, bad, SUSPEND), lambda: B.gcaps_gprio_rta_batch(ctx, bad, SUSPEND, gprio)):
+        with pytest.raises(B.GcapsError) as e:
+            call()
+        assert e.value.first_bad == N // 2
+    compare(oracle, B, ctx, batch, skip, waits=(BUSY,))
+
+
+@pytest.mark.parametrize("cores,per_core,N", [(1, 2, 98_305), (4, 4, 98_305), (2, 4, 16_385)])
+def test_lanes_per_taskset_at_the_upper_lines(oracle, gpu, cores, per_core, N):
+    B, ctx, _ = gpu
+    batch = relaxed_workload(N, seed=7, n_cores=cores, per_core=per_core, S=1)
+    for n_used in (N - 1, N):
+        part = {k: v[:n_used] for k, v in batch.items()}
+        compare(oracle, B, ctx, part, waits=(SUSPEND,))
+        want_r, want_s = oracle.gprio_rta_batch(part, part["prio"], SUSPEND)
+        got_r, got_s = B.gcaps_gprio_rta_batch(ctx, part, SUSPEND, part["prio"])
+        assert (got_r == want_r).all() and (got_s == want_s).all()
+
+
 def test_analysis_for_given_priorities(oracle, gpu):
     from paper_2406_05221_amd import taskgen
     B, ctx, _ = gpu

@@ -598,6 +598,22 @@ def test_continue_after_miss_shapes(oracle, gpu, shape):
         compare_continue(oracle, B, relaxed_workload(N, seed=N, n_cores=cores, per_core=per_core, S=S))
 
 
+@pytest.mark.parametrize("cores,per_core,S", [(1, 2, 1), (2, 3, 3), (4, 5, 3), (4, 6, 8), (5, 5, 3)])
+@pytest.mark.parametrize("N", [3, 4_097, 9_217, 24_576, 24_577])
+def test_continue_after_miss_small_calls(oracle, gpu, cores, per_core, S, N):
+    """Up to 96 tasksets per CU and 24 tasks in the form of the small calls (256 compute units: lines at 4,096, 9,216 and 24,576
+    tasksets); a taskset in which a committed cost leaves the 24-bit range is redone where it is found."""
+    B, _, _ = gpu
+    batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
+    rng = np.random.default_rng(N)
+    odd = np.unique(np.concatenate([[0, N - 1], rng.integers(0, N, N // 40)]))
+    batch["cpu_us"][odd, 0] = 2**23
+    batch["period_us"][odd, 0] = 2**25
+    batch["deadline_us"][odd, 0] = 2**25
+    assert compare_continue(oracle, B, batch) >= odd.size
+    compare_continue(oracle, B, batch, GCAPS, waits=(SUSPEND,))
+
+
 def test_continue_after_miss_mixed_cases(oracle, gpu):
     B, _, _ = gpu
     rng = np.random.default_rng(15)
