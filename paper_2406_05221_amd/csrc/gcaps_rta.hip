@@ -297,18 +297,37 @@ int launch_fast_np(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mo
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
+/* Tasksets per wavefront of the screen.  A tile keeps a row of LDS per task: with 80 tasks of 64 tasksets a compute unit holds six
+ * wavefronts, with 32 thirteen, whose loads cover each other, and 100,000 tasksets are one round of them instead of one and a
+ * little.  Fewer tasks leave room for enough of either, and the wider tile keeps all lanes at work in the walk; a batch of up to 256
+ * tasksets per CU has too few wide tiles.  us with 64 / 32, both policies, busy-waiting, overloaded: 80 tasks x 5 segments, 5,000 tasksets 55.7 / 42.3,
+ * 100,000 137.8 / 109.3, 200,000 215.2 / 168.6; 80 x 3, 100,000 166.9 / 141.3; 40 x 5, 100,000 87.5 / 95.0, 200,000 140.0 / 130.9;
+ * 40 x 3, 65,536 90.2 / 91.9, 400,000 210.0 / 195.6; 32 x 6, 100,000 78.8 / 86.4, 400,000 178.2 / 179.6; 32 x 3, 100,000 89.3 / 84.6,
+ * 400,000 182.0 / 168.7; 24 x 3, 33,333 60.9 / 58.8, 100,000 71.0 / 72.7; 20 x 3, 65,536 56.8 / 55.3, 400,000 127.0 / 139.4. */
+u32 screen_width(const gcaps_ctx *ctx, const gcaps_batch *b) {
+  const u32 n = b->n_tasks;
+  return n > 32u || (n > 24u && b->max_gseg <= 4u) || b->n_tasksets <= 256u * (u32)ctx->n_cu ? 32u : 64u;
+}
+
 int launch_screen(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp,
-                  uint8_t *d_sched, u32 kr, u32 blocks) {
-  const size_t lds = fast::lds_bytes(b->n_tasks, kr, 64, true);
+                  uint8_t *d_sched, u32 kr) {
   const fast::ListSpec dl = deep_list_spec(ctx, false);
-  if (wait_mode == GCAPS_WAIT_BUSY)
-    hipLaunchKernelGGL(fast::rta_screen_kernel<true>, dim3(blocks), dim3(64), lds, ctx->stream, *b, policy,
-                       (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
+  auto launch = [&](auto busy, auto segs, auto ts) {
+    constexpr u32 TS = decltype(ts)::value;
+    hipLaunchKernelGGL((fast::rta_screen_kernel<decltype(busy)::value, decltype(segs)::value, (int)TS>),
+                       dim3((b->n_tasksets + TS - 1u) / TS), dim3(64), fast::lds_bytes(b->n_tasks, kr, TS, true), ctx->stream, *b,
+                       policy, (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
                        ctx->resp_stride, ctx->sched_stride, ctx->ts_offset);
-  else
-    hipLaunchKernelGGL(fast::rta_screen_kernel<false>, dim3(blocks), dim3(64), lds, ctx->stream, *b, policy,
-                       (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
-                       ctx->resp_stride, ctx->sched_stride, ctx->ts_offset);
+  };
+  auto with_segs = [&](auto busy, auto segs) {
+    if (screen_width(ctx, b) == 32u) launch(busy, segs, std::integral_constant<int, 32>{});
+    else launch(busy, segs, std::integral_constant<int, 64>{});
+  };
+  auto with = [&](auto busy) {
+    if (b->max_gseg <= (u32)fast::kCacheSegs) with_segs(busy, std::integral_constant<int, fast::kCacheSegs>{});
+    else with_segs(busy, std::integral_constant<int, fast::kPrefetchSegs>{});
+  };
+  if (wait_mode == GCAPS_WAIT_BUSY) with(std::true_type{}); else with(std::false_type{});
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -318,8 +337,10 @@ template <int TS>
 int launch_fast(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp,
                 uint8_t *d_sched, u32 kr, u32 blocks) {
   if constexpr (TS == 64) {
-    if (kr <= (u32)fast::kCacheRanks && b->max_gseg <= (u32)fast::kCacheSegs && b->n_tasks <= 255)
-        return launch_screen(ctx, b, policy, wait_mode, d_resp, d_sched, kr, blocks);
+    /* us in the general form / in the screen, as above: 80 tasks x 5 segments, 5,000 tasksets 48.8 / 42.3, 100,000 160.4 / 109.3; 56 x 5,
+     * 200,000 221.0 / 139.1; 32 x 6, 400,000 302.5 / 178.2; 20 x 5, 5,000 49.0 / 42.6, 400,000 233.6 / 133.0 */
+    if (kr <= (u32)fast::kCacheRanks && b->max_gseg <= (u32)fast::kPrefetchSegs && b->n_tasks <= 255)
+        return launch_screen(ctx, b, policy, wait_mode, d_resp, d_sched, kr);
     if (kr <= 4) return launch_fast_np<TS, 4>(ctx, b, policy, wait_mode, d_resp, d_sched, kr, blocks);
     if (kr <= 8) return launch_fast_np<TS, 8>(ctx, b, policy, wait_mode, d_resp, d_sched, kr, blocks);
     if (kr <= 16) return launch_fast_np<TS, 16>(ctx, b, policy, wait_mode, d_resp, d_sched, kr, blocks);
@@ -1105,7 +1126,11 @@ extern "C" int gcaps_create(gcaps_ctx **out, int device_id, void *hip_stream) {
         (const void *)fast::rta_fast_kernel<64, 8>,  (const void *)fast::rta_fast_kernel<64, 16>,
         (const void *)fast::rta_fast_kernel<64, 24>, (const void *)fast::rta_fast_kernel<64, 32>,
         (const void *)fast::rta_fast_kernel<32, 0>,  (const void *)fast::rta_fast_kernel<16, 0>,
-        (const void *)fast::rta_screen_kernel<true>, (const void *)fast::rta_screen_kernel<false>,
+#define GCAPS_SCREEN_KERNELS(SEGS)                                                                                \
+  (const void *)fast::rta_screen_kernel<true, SEGS, 32>, (const void *)fast::rta_screen_kernel<false, SEGS, 32>,  \
+      (const void *)fast::rta_screen_kernel<true, SEGS, 64>, (const void *)fast::rta_screen_kernel<false, SEGS, 64>
+        GCAPS_SCREEN_KERNELS(fast::kCacheSegs), GCAPS_SCREEN_KERNELS(fast::kPrefetchSegs),
+#undef GCAPS_SCREEN_KERNELS
         (const void *)fast::rta_deep_kernel<true, 4, false>, (const void *)fast::rta_deep_kernel<false, 4, false>,
         (const void *)fast::rta_deep_kernel<true, 8, false>, (const void *)fast::rta_deep_kernel<false, 8, false>,
         (const void *)fast::rta_deep_kernel<true, 4, true>, (const void *)fast::rta_deep_kernel<false, 4, true>,

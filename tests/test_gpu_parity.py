@@ -614,6 +614,35 @@ def test_continue_after_miss_small_calls(oracle, gpu, cores, per_core, S, N):
     compare_continue(oracle, B, batch, GCAPS, waits=(SUSPEND,))
 
 
+@pytest.mark.parametrize("cores,per_core,S", [(1, 1, 5), (4, 5, 3), (4, 5, 6), (4, 6, 7), (4, 7, 4), (4, 8, 8), (3, 11, 5), (8, 10, 5), (8, 10, 0), (5, 20, 2)])
+@pytest.mark.parametrize("N", [1, 31, 33, 2_017])
+def test_screen_tile_widths(oracle, monkeypatch, cores, per_core, S, N):
+    """The first launch in tiles of 32 tasksets (its smaller batches and its many tasks), up to eight segment slots: ragged last tiles,
+    an invalid taskset, one outside the 24-bit range."""
+    import torch
+    from paper_2406_05221_amd import binding as B
+    monkeypatch.setenv("GCAPS_ONE_LAUNCH", "0")
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
+        batch["period_us"][N - 1, 0] = batch["deadline_us"][N - 1, 0] = 2**25
+        for policy in (BOTH, GCAPS):
+            compare(oracle, B, ctx, batch, policy)
+        bad = {k: v.copy() for k, v in batch.items()}
+        bad["period_us"][N // 2, 0] = 0
+        with pytest.raises(B.GcapsError) as e:
+            B.gcaps_rta_batch(ctx, bad, BOTH, SUSPEND)
+        assert e.value.first_bad == N // 2
+    finally:
+        B.gcaps_destroy(ctx)
+
+
+@pytest.mark.parametrize("S,N", [(3, 65_536), (3, 65_537), (6, 65_537)])
+def test_screen_width_at_its_line(oracle, gpu, S, N):
+    B, ctx, _ = gpu
+    compare(oracle, B, ctx, relaxed_workload(N, seed=S, n_cores=4, per_core=5, S=S))
+
+
 def test_continue_after_miss_mixed_cases(oracle, gpu):
     B, _, _ = gpu
     rng = np.random.default_rng(15)
