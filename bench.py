@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="f3081f2b2c79a713031f1dbe67e98ae4fd5c335f589c62e0400aa0fa6550b1de", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=56_958_993, valu_lane_ops=2_598_554_605),
-                            suspend=dict(valu_wave_insts=61_951_889, valu_lane_ops=2_698_825_778)),
-                  "0": dict(busy=dict(valu_wave_insts=355_111_445, valu_lane_ops=20_370_791_057),
-                            suspend=dict(valu_wave_insts=529_758_975, valu_lane_ops=30_349_539_092))})
+    csrc_sha256="9b0785c53ab94305096a0c562506b6d1d1258bee501ebc843addd4e79e23aeb0", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=56_962_893, valu_lane_ops=2_598_784_221),
+                            suspend=dict(valu_wave_insts=61_959_281, valu_lane_ops=2_699_261_689)),
+                  "0": dict(busy=dict(valu_wave_insts=355_112_752, valu_lane_ops=20_370_862_350),
+                            suspend=dict(valu_wave_insts=529_792_558, valu_lane_ops=30_351_477_073))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="f3081f2b2c79a713031f1dbe67e98ae4fd5c335f589c62e0400aa0fa6550b1de",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915934860, write_bytes=328834480)
+MEASURED_TRAFFIC = dict(csrc_sha256="9b0785c53ab94305096a0c562506b6d1d1258bee501ebc843addd4e79e23aeb0",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915859547, write_bytes=328828251)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="13c317f7a743a2ad6ad365d5f719d4bbfbe59a7ae41c0b02f89891c6a100438e",
-                              workload=3, tasksets=1_000_000, fetch_bytes=878001629, write_bytes=242012659)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="111b11f94673dfabe26b0e2d45553365b660b6969398d0b52b61066ea9b64b17",
+                              workload=3, tasksets=1_000_000, fetch_bytes=877797970, write_bytes=242013691)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged
