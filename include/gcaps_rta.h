@@ -173,7 +173,8 @@ int gcaps_rta_batch(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wa
  * violations are detected on the device and reported by gcaps_status().
  * The verdict of an invalid taskset is 0 and its response times are undefined; the outputs of all others are complete.
  * The launches of a call may be recorded into a HIP graph (stream capture) once a direct call with
- * the same sizes has been made on the context: that call makes the device allocations, a recorded
+ * the same sizes has been made on the context, with any policy and waiting mode and with or without continue-after-miss
+ * (with gcaps_set_binning as when recording): that call makes the device allocations, a recorded
  * one makes none (GCAPS_ESIZE when it would have to).  A direct call that needs more scratch than any before
  * it frees and reallocates the context's buffers: graphs recorded earlier on this context then point
  * to freed memory and must be recorded again.  A recorded call depends on no earlier call and can be

@@ -564,6 +564,20 @@ int tile_width(const gcaps_ctx *ctx, u32 n, u32 kr) {
   return 0;
 }
 
+/* Slots per region of the list between the two fast launches.  Tiles of the first launch go to the regions round-robin: a region
+ * never overflows (16: the narrowest tile). */
+u32 region_slots(u32 N) { return ((N + 15u) / 16u + fast::kListRegions - 1u) / fast::kListRegions * 64u; }
+
+/* The lists of a call of N tasksets in two launches.  A direct call in one launch reserves them as well, behind its launches and
+ * without failing where there is no memory for them: a recorded call of the same sizes finds what it needs, whatever its
+ * policy and mode. */
+int reserve_lists(gcaps_ctx *ctx, u32 N) {
+  const size_t deep = (size_t)region_slots(N) * fast::kListRegions * sizeof(u32);
+  int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
+  if (rc == GCAPS_OK) rc = ctx->pool.deep_list.reserve(deep, !ctx->capturing);
+  if (rc == GCAPS_OK && ctx->binning) rc = ctx->pool.deep_aux.reserve(2 * deep, !ctx->capturing);
+  return rc;
+}
 
 /* one chunk: every array of it stays below 4 GiB, so the kernels index with 32 bits */
 int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp,
@@ -582,7 +596,9 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
     /* With a column for every taskset what is outside the fast range is redone where it is found.  Columns that are not there yet
      * are allocated by a launch over a list behind this one, while this one runs (a context's first call of 9,000 tasksets of 16
      * tasks: 45 us, 54 with the allocation in front of the only launch). */
-    return launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws);
+    const int rc = launch_small_any(ctx, b, policy, wait_mode, d_resp, d_sched, ws);
+    if (rc == GCAPS_OK && !ctx->capturing) (void)reserve_lists(ctx, N);
+    return rc;
   }
   int rc = ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
   if (rc != GCAPS_OK) return rc;
@@ -594,16 +610,14 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
                                   : launch_deep(ctx, b, policy, wait_mode, d_resp, d_sched, 0u);
     if (rc != GCAPS_OK) return rc;
     const u32 *count = (const u32 *)status_of(ctx) + fast::ST_WIDE_COUNT;
-    return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, (const u32 *)ctx->pool.wide_list.ptr, count,
-                       N < 65536u ? N : 65536u);
+    rc = launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, (const u32 *)ctx->pool.wide_list.ptr, count,
+                     N < 65536u ? N : 65536u);
+    if (rc == GCAPS_OK && !ctx->capturing) (void)reserve_lists(ctx, N);
+    return rc;
   }
 
-  /* tiles of the first launch go to the list regions round-robin: a region never overflows */
-  const u32 producer_tiles = (N + 15u) / 16u; /* the narrowest tile width */
-  ctx->region_cap = ((producer_tiles + fast::kListRegions - 1) / fast::kListRegions) * 64u;
-  rc = ctx->pool.deep_list.reserve((size_t)ctx->region_cap * fast::kListRegions * sizeof(u32), !ctx->capturing);
-  if (rc == GCAPS_OK && ctx->binning)
-    rc = ctx->pool.deep_aux.reserve((size_t)ctx->region_cap * fast::kListRegions * 2 * sizeof(u32), !ctx->capturing);
+  ctx->region_cap = region_slots(N);
+  rc = reserve_lists(ctx, N);
   if (rc != GCAPS_OK) return rc;
   /* first launch: every taskset, the kr highest-priority tasks only */
   const u32 tiles = (N + (u32)ts_screen - 1) / (u32)ts_screen;

@@ -783,6 +783,52 @@ def test_recorded_call_in_one_launch_needs_no_list(oracle, monkeypatch):
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("per_cu,S,direct,recorded,columns_first", [
+    (120, 3, (BOTH, 0), (RR, 0), False), (120, 3, (GCAPS, 0), (RR, 0), True), (120, 3, (BOTH, 0), (BOTH, 1), True),
+    (80, 5, (BOTH, 1), (RR, 0), False), (80, 5, (RR, 1), (GCAPS, 0), True), (120, 3, (RR, 0), (BOTH, 0), False)])
+def test_recorded_call_after_a_direct_one_on_another_route(oracle, gpu, per_cu, S, direct, recorded, columns_first):
+    """After a direct call a recorded one of the same sizes is not refused, whatever its policy and mode: between the lines of
+    the one-launch form (which differ by policy, and from that of continue-after-miss) the two need different buffers.
+    `columns_first`: the columns of the 64-bit kernel are there before the direct call, which then lists nothing."""
+    import torch
+    B, _, _ = gpu
+    stream = torch.cuda.Stream()
+    ctx = B.gcaps_create(0, stream.cuda_stream)
+    try:
+        N = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + 1
+        batch = relaxed_workload(N, seed=per_cu + S, S=S)
+        if columns_first:
+            large = relaxed_workload(N // 4, seed=1, per_core=25, S=1)
+            B.gcaps_gprio_rta_batch(ctx, large, BUSY, large["prio"])
+        d = B.to_device(batch)
+        n = batch["cpu_us"].shape[1]
+        outputs = {}
+        for policy in {direct[0], recorded[0]}:
+            P = B.npol(policy)
+            outputs[policy] = (torch.empty((P, N, n), dtype=torch.int64, device="cuda:0"),
+                               torch.empty((P, N), dtype=torch.uint8, device="cuda:0"))
+        B.gcaps_set_continue_after_miss(ctx, direct[1])
+        B.gcaps_rta_batch_device(ctx, d, direct[0], BUSY, *outputs[direct[0]])
+        B.gcaps_status(ctx)
+        B.gcaps_set_continue_after_miss(ctx, recorded[1])
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.gcaps_rta_batch_device(ctx, d, recorded[0], BUSY, *outputs[recorded[0]])
+        want_r, want_s, _ = oracle.rta_batch(batch, recorded[0], BUSY, threads=16,
+                                             options=oracle.OPT_CONTINUE_AFTER_MISS if recorded[1] else 0)
+        for k in range(3):
+            for out in outputs[recorded[0]]:
+                out.fill_(9)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            resp, sched = outputs[recorded[0]]
+            assert np.array_equal(resp.cpu().numpy(), want_r) and np.array_equal(sched.cpu().numpy(), want_s), k
+            B.gcaps_rta_batch(ctx, relaxed_workload(700, seed=k), BOTH, SUSPEND)
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_argument_and_allocation_failures_leave_the_context_usable(oracle, gpu):
     """Failures forced from the host: an empty batch (GCAPS_EINVAL) and a batch whose device copy cannot be
     allocated (GCAPS_ENOMEM: the sizes ask for petabytes; no array is touched before the allocation fails)."""
