@@ -393,7 +393,7 @@ int launch_quad(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_res
   if (blocks > max_tiles) blocks = max_tiles;
   hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, ALL>), dim3(blocks), dim3(64), lds, ctx->stream, *b,
                      policy, (long long *)d_resp, d_sched, status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, kr,
-                     ctx->resp_stride, ctx->sched_stride, ctx->ts_offset, ctx->cont != 0, wide::Scratch{}, (u32 *)nullptr);
+                     ctx->resp_stride, ctx->sched_stride, ctx->ts_offset, ctx->cont != 0, fast::NoRedo{});
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
@@ -440,7 +440,7 @@ int launch_small(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_re
   hipLaunchKernelGGL((fast::rta_quad_kernel<BUSY, NSMAX, SEGS, true, Q, 2>), dim3((N + ts - 1u) / ts), dim3(128),
                      fast::quad_lds_bytes(n, (u32)Q, 2u), ctx->stream, *b, policy, (long long *)d_resp, d_sched,
                      status_of(ctx), (u32 *)ctx->pool.wide_list.ptr, dl, 0u, ctx->resp_stride, ctx->sched_stride,
-                     ctx->ts_offset, ctx->cont != 0, ws, ctx->next_status);
+                     ctx->ts_offset, ctx->cont != 0, fast::SmallRedo{ws, ctx->next_status});
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
