@@ -829,6 +829,34 @@ def test_recorded_call_after_a_direct_one_on_another_route(oracle, gpu, per_cu, 
         B.gcaps_destroy(ctx)
 
 
+@pytest.mark.parametrize("call,per_core,per_cu", [("rta", 1, 160), ("search", 2, 64), ("given", 3, 64), ("given", 7, 48)])
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_calls_outside_the_24_bit_range(oracle, gpu, call, per_core, per_cu, beyond):
+    """At most so many tasksets per CU are redone in 64 bit where they are found, more of them by a launch over a list: every
+    taskset is outside the range, all of them twice (the first call of a context has a list in any case)."""
+    import torch
+    B, _, _ = gpu
+    N = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + beyond
+    batch = relaxed_workload(N, seed=per_core, per_core=per_core, S=1)
+    for key in ("cpu_us", "period_us", "deadline_us", "gm_us", "ge_us"):
+        batch[key] = np.minimum(batch[key].astype(np.uint64) * 300, 2**32 - 1).astype(np.uint32)
+    ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
+    try:
+        for _ in range(2):
+            if call == "rta":
+                compare(oracle, B, ctx, batch, waits=(SUSPEND,))
+            elif call == "search":
+                got = B.gcaps_gprio_assign_batch(ctx, batch, BUSY)
+                assert all(np.array_equal(x, y) for x, y in zip(got, oracle.gprio_assign_batch(batch, BUSY, threads=16)[:3]))
+            else:
+                got = B.gcaps_gprio_rta_batch(ctx, batch, SUSPEND, batch["prio"])
+                want = oracle.gprio_rta_batch(batch, batch["prio"], SUSPEND)
+                assert all(np.array_equal(x, y) for x, y in zip(got, want))
+            assert B.gcaps_last_wide_count(ctx) == N
+    finally:
+        B.gcaps_destroy(ctx)
+
+
 def test_argument_and_allocation_failures_leave_the_context_usable(oracle, gpu):
     """Failures forced from the host: an empty batch (GCAPS_EINVAL) and a batch whose device copy cannot be
     allocated (GCAPS_ENOMEM: the sizes ask for petabytes; no array is touched before the allocation fails)."""
