@@ -515,24 +515,33 @@ bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
 /* One full-depth launch for the whole call instead of two with a list between them and a third behind.  A small call is
  * bound by latency: the chain of dependent loads of a launch, and the launches behind it.  A large one is bound by work,
  * most of which the first launch of the two saves where tasksets miss their deadlines within its ranks; it stages no segments
- * of further ranks.  How many do is not known here: the lines lie below where a batch that misses at once (periods from
- * 500, overheads of 300, half to nine tenths of every core used; the round-robin pass alone always does) or one of mixed
- * load takes as long either way.  us in two launches / in one, both policies, self-suspension, a batch that misses at once; then
- * a mixed one:
- *   1 task, 16,384 tasksets 15.3 / 10.0, 13.4 / 9.7, 32,768 13.6 / 12.1; 2 tasks, 24,576 14.4 / 9.7, 32,768 14.5 / 13.4;
- *   6 x 1 segment, 8,000 32.4 / 11.7, 31.7 / 10.9; 49,152 38.6 / 27.1, 49.9 / 26.8; 98,304 43.4 / 47.9;
- *   20 x 3, 8,000 30.4 / 12.2, 62.7 / 30.4; 49,152 36.8 / 28.6, 88.0 / 82.1; 65,536 38.1 / 33.0, 99.6 / 101.7;
- *   24 x 4, 32,768 32.1 / 24.1, 84.2 / 83.9; 49,152 34.4 / 30.7, 100.0 / 106.0;
- *   20 x 5, 49,152 45.1 / 37.6, 106.6 / 91.1; 24 x 8, 24,576 34.2 / 30.4, 106.4 / 65.6; 32,768 36.4 / 43.1.
- * Round-robin alone, a batch that misses at once: 20 x 3, 16,384 18.2 / 10.4, 32,768 19.2 / 18.7; 24 x 4, 16,384 20.6 / 12.7,
- * 32,768 21.2 / 22.4; 20 x 5, 16,384 16.3 / 14.0, 32,768 18.0 / 25.9; 24 x 8, 16,384 18.7 / 22.1. */
+ * of further ranks.  How many do is not known here: the lines lie where a batch that misses at once (periods from
+ * 500, overheads of 300, half to nine tenths of every core used; the round-robin pass alone always does) loses no more in one launch
+ * than batches of mixed and of light load save.  Above 96 tasksets per CU not all wavefronts of four lanes per taskset are resident at
+ * once.  GCAPS alone takes as long as both policies, each having a wavefront; in two launches it is quicker by one pass of the first,
+ * which counts where a taskset has many segments.  us in two launches / in one, both policies, self-suspension, a batch that
+ * misses at once (inputs read for the first time, 650 MB of others before them); a mixed one; a lightly loaded one:
+ *   2 tasks, 16,384 tasksets 11.3 / 7.3 (11.4 / 7.6); 11.4 / 7.3;
+ *   6 x 1 segment, 49,152 34.3 / 25.2 (37.5 / 28.3); 43.7 / 27.4;
+ *   20 x 3, 24,576 26.0 / 14.3 (28.4 / 17.4); 50.6 / 32.6; 70.3 / 39.4; 49,152 27.9 / 26.3 (31.7 / 27.8); 54.5 / 49.7; 88.1 / 79.7;
+ *   24 x 3, 49,152 29.2 / 27.3 (30.9 / 29.2); 67.3 / 57.1;
+ *   20 x 4, 32,768 26.3 / 22.7 (27.8 / 24.5); 52.3 / 40.9; 24 x 4, 24,576 19.6 / 14.9 (22.9 / 18.8); 58.6 / 39.4; 32,768 20.4 / 24.0
+ *   (23.5 / 26.2); 59.5 / 47.8; 40,960 20.6 / 26.4 (27.3 / 29.2); 61.3 / 51.0;
+ *   20 x 5, 24,576 27.2 / 18.0 (29.0 / 20.0); 49.9 / 32.3; 49,152 28.1 / 36.5 (30.9 / 41.9); 56.4 / 48.3; 82.3 / 67.2 (46,080);
+ *   24 x 6, 24,576 20.8 / 18.1 (23.7 / 21.9); 54.4 / 37.9;
+ *   24 x 8, 12,288 19.5 / 19.9 (22.2 / 20.7); 51.2 / 41.3; 16,384 19.8 / 22.8 (21.3 / 23.6); 55.2 / 48.1; 80.1 / 50.4; 24,576 20.0 / 29.5
+ *   (21.9 / 30.8); 57.5 / 52.6; 95.1 / 62.9; GCAPS alone 12,288 17.7 / 19.7 (21.1 / 20.4); 48.9 / 40.7; 24,576 18.0 / 29.0 (21.2 / 29.9).
+ * Round-robin alone, a batch that misses at once: 20 x 3, 24,576 13.4 / 10.8 (14.2 / 13.6), 32,768 13.6 / 17.7; 24 x 4, 24,576
+ * 15.2 / 13.0 (17.0 / 16.9), 28,672 15.6 / 20.6; 20 x 5, 16,384 13.5 / 12.6 (14.9 / 15.8), lightly loaded 15,360 24.6 / 13.8 (27.5 / 17.2);
+ * 20 x 8, 8,192 0.99 (0.99) times as long in one, 10,240 13.5 / 17.0; 24 x 8, 8,192 0.92 (0.88), 12,288 15.5 / 18.9. */
 bool one_launch_applies(const gcaps_ctx *ctx, const gcaps_batch *b, int policy) {
   if (ctx->binning || ctx->screen_tasks != 4u || !quad_all_applies(ctx, b)) return false;
   if (ctx->one_launch >= 0) return b->n_tasksets <= (u32)ctx->one_launch;
   const u32 n = b->n_tasks, S = b->max_gseg;
   if (n > kSmallTasks) return false;
-  const bool rr = policy == GCAPS_POLICY_RR, large = S > 4u && n * S > 100u;
-  u32 per_cu = large ? (rr ? 32u : 96u) : S > 4u ? (rr ? 64u : 192u) : S == 4u ? (rr ? 80u : 128u) : rr ? 96u : 192u;
+  const u32 slots = n * S;
+  const bool rr = policy == GCAPS_POLICY_RR, large = S > 4u && slots > 100u;
+  u32 per_cu = large ? (rr ? 32u : slots <= 144u ? 96u : policy == GCAPS_POLICY_BOTH ? 80u : 48u) : S > 4u ? (rr ? 64u : 192u) : S == 4u ? (rr ? 80u : 128u) : rr ? 96u : 192u;
   if (n <= 4u && per_cu > 64u) per_cu = 64u;
   return b->n_tasksets <= (u32)ctx->n_cu * per_cu;
 }

@@ -437,15 +437,19 @@ def test_small_calls_by_lanes_per_taskset(oracle, gpu, cores, per_core, S, N):
     compare(oracle, B, ctx, batch)
 
 
-@pytest.mark.parametrize("cores,per_core,S,N", [(1, 2, 1, 1_000), (1, 3, 1, 8_192), (1, 5, 4, 16_384), (2, 3, 3, 16_384), (4, 4, 3, 24_576),
-                                                (4, 5, 3, 19_660), (4, 6, 4, 8_192), (4, 6, 8, 4_096), (4, 5, 5, 9_830), (5, 5, 3, 1_000)])
-def test_default_route_at_its_lines(oracle, gpu, cores, per_core, S, N):
-    """The largest call of a shape that takes one launch by default and one taskset more (both policies; round-robin alone
-    takes half as many), shapes that never do: the same results."""
+@pytest.mark.parametrize("cores,per_core,S,both,gcaps,rr", [
+    (1, 2, 1, 64, 64, 64), (2, 3, 3, 192, 192, 96), (4, 5, 3, 192, 192, 96), (4, 6, 4, 128, 128, 80), (4, 5, 5, 192, 192, 64),
+    (3, 7, 5, 96, 96, 32), (4, 6, 6, 96, 96, 32), (4, 5, 8, 80, 48, 32), (4, 6, 8, 80, 48, 32), (5, 5, 3, 4, 4, 4)])
+def test_default_route_at_its_lines(oracle, gpu, cores, per_core, S, both, gcaps, rr):
+    """The largest call of a shape that takes one launch by default (in tasksets per compute unit; of 25 tasks none does) and one taskset
+    more, for both policies, GCAPS alone and round-robin alone: the same results."""
+    import torch
     B, ctx, _ = gpu
-    batch = relaxed_workload(N + 1, seed=N, n_cores=cores, per_core=per_core, S=S)
-    for policy, size in ((BOTH, N), (BOTH, N + 1), (RR, N // 2), (RR, N // 2 + 1)):
-        compare(oracle, B, ctx, {k: v[:size] for k, v in batch.items()}, policy, waits=(SUSPEND,))
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    batch = relaxed_workload(both * cu + 1, seed=both, n_cores=cores, per_core=per_core, S=S)
+    for policy, line in ((BOTH, both), (GCAPS, gcaps), (RR, rr)):
+        for size in (line * cu, line * cu + 1):
+            compare(oracle, B, ctx, {k: v[:size] for k, v in batch.items()}, policy, waits=(SUSPEND,))
 
 
 def test_out_of_range_values_below_the_screened_ranks(oracle, gpu):
