@@ -445,11 +445,16 @@ int launch_small(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int64_t *d_re
 }
 
 /* Lanes per taskset: the more, the fewer terms a lane sums and the fewer tasksets walk in lock step, but the more
- * wavefronts.  Sixteen while those are at most about two per SIMD, eight up to nine wavefronts per CU.  us with
- * 4 / 8 / 16 lanes, both policies, self-suspension: 6 tasks, 1,000 tasksets 9.9 / 9.5 / 9.2, 8,000 11.3 / 10.8 / 12.3; 16 tasks x 3
- * segments, lightly loaded, 3,000 20.2 / 18.1 / 17.1, 9,000 21.2 / 23.6 / 35.6 (overloaded 13.9 / 12.6 / 14.0, mixed 24.1 / 24.9 /
- * 35.5); 20 x 3, 770 25.4 / 22.1 / 19.8, 9,000 26.7 / 29.7 / 42.2 (13.6 / 12.2 / 12.7, 31.4 / 30.4 / 43.9), 19,000
- * 36.8 / 49.3 / 65.7; 24 x 3, 3,000 30.6 / 26.9 / 24.2, 8,000 32.1 / 29.0 / 35.0. */
+ * wavefronts.  Sixteen while those are at most about two per SIMD; eight up to a line that lies the higher the more terms there are to
+ * share.  us with 4 / 8 / 16 lanes, both policies, self-suspension or busy-waiting, three segments, lightly loaded (overloaded;
+ * mixed; inputs not in a cache move the lines by less than their steps):
+ *   4 tasks, 7,680 tasksets 8.7 / 8.2, 9,216 8.7 / 9.0; 6, 4,096 10.4 / 10.0 / 10.6, 7,680 10.8 / 10.6 / 13.3 (10.5 / 9.9 / 11.1;
+ *   11.3 / 11.0 / 13.4), 9,216 10.7 / 11.9 (10.6 / 10.7; 11.8 / 12.3); 8, 7,680 12.2 / 11.3, 9,216 12.1 / 12.5 (11.3 / 11.0; 13.0 / 12.9);
+ *   10, 9,216 14.8 / 15.2 (13.4 / 12.4; 16.5 / 15.5), 10,752 15.0 / 16.2 (13.4 / 13.1; 16.6 / 16.2); 12, 9,216 16.1 / 16.7 (14.9 / 13.3;
+ *   17.0 / 17.0), 12,288 16.0 / 17.7;
+ *   16, 4,096 22.5 / 20.4 / 19.5, 5,120 23.6 / 20.4 / 22.1, 12,288 20.1 / 20.5 (11.6 / 10.5; 20.7 / 20.2), 16,384 25.4 / 25.8 (13.8 / 13.1;
+ *   24.8 / 23.0); 20, 12,288 31.4 / 32.5 (11.7 / 11.6; 29.6 / 26.9), 16,384 31.6 / 33.5; 24, 4,096 35.0 / 31.7 / 27.8, 5,120
+ *   37.8 / 31.7 / 31.2, 12,288 37.9 / 37.5 (11.7 / 11.0; 36.7 / 33.5). */
 int launch_small_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp, uint8_t *d_sched,
                      const wide::Scratch &ws) {
   const bool busy = wait_mode == GCAPS_WAIT_BUSY;
@@ -459,7 +464,7 @@ int launch_small_any(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_
         : launch_small<false, NS, SEGS, Q>(ctx, b, policy, d_resp, d_sched, ws))
 #define GCAPS_SMALL(NS, Q) (b->max_gseg <= 3 ? GCAPS_SMALL_S(NS, 3, Q) : GCAPS_SMALL_S(NS, fast::kPrefetchSegs, Q))
   if (N <= 16u * cu) return n <= 16 ? GCAPS_SMALL(1, 16) : GCAPS_SMALL(2, 16);
-  if (N <= 36u * cu) return n <= 16 ? GCAPS_SMALL(2, 8) : GCAPS_SMALL(3, 8);
+  if (N <= (n <= 8 ? 30u : n <= 12 ? 36u : 48u) * cu) return n <= 16 ? GCAPS_SMALL(2, 8) : GCAPS_SMALL(3, 8);
   return n <= 20 ? GCAPS_SMALL(5, 4) : GCAPS_SMALL(6, 4);
 #undef GCAPS_SMALL
 #undef GCAPS_SMALL_S

@@ -411,10 +411,10 @@ def test_calls_in_one_launch_and_in_two(oracle, monkeypatch, shape, tasksets):
 
 
 @pytest.mark.parametrize("cores,per_core,S", [(1, 1, 1), (1, 3, 8), (4, 4, 3), (1, 17, 4), (4, 5, 0), (3, 7, 3), (4, 6, 8)])
-@pytest.mark.parametrize("N", [1, 3, 5, 4_096, 4_097, 9_217])
+@pytest.mark.parametrize("N", [1, 3, 5, 4_096, 4_097, 7_681, 9_217, 12_289])
 def test_small_calls_by_lanes_per_taskset(oracle, gpu, cores, per_core, S, N):
-    """A small call gives a taskset sixteen, eight or four lanes by its size (256 compute units: up to 4,096 and up to 9,216
-    tasksets), a wavefront per policy; term registers for up to 16, 20 and 24 tasks; tasksets outside the 24-bit range
+    """A small call gives a taskset sixteen, eight or four lanes by its size and shape (256 compute units: up to 4,096 and up to 7,680,
+    9,216 or 12,288 tasksets), a wavefront per policy; term registers for up to 16, 20 and 24 tasks; tasksets outside the 24-bit range
     are redone where they are found, the first and the last of a tile among them, and are counted."""
     B, ctx, _ = gpu
     batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
