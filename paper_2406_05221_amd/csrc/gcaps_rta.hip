@@ -139,6 +139,7 @@ struct gcaps_ctx {
   u64 chunk_cap = 0;        /* GCAPS_CHUNK_TASKSETS: smaller chunks than the 32-bit limit needs (testing) */
   u32 sim_blocks_cap = 0;   /* GCAPS_SIM_BLOCKS: fewer workgroups per simulation launch than fit the GPU (testing:
                                every lane then takes many tasksets) */
+  u32 screen_width = 0;     /* GCAPS_SCREEN_WIDTH: tasksets per wavefront of the first fast launch, 32 or 64 (0: by the rule; testing) */
   u32 screen_tasks = 4;     /* tasks per taskset analysed by the first fast launch (GCAPS_SCREEN_TASKS) */
   int one_launch = -1;      /* GCAPS_ONE_LAUNCH: calls of at most this many tasksets take one launch (-1: by the rule) */
   u32 deep_lanes = 4;       /* lanes per taskset in the second fast launch, 4 or 8 (GCAPS_DEEP_LANES) */
@@ -297,16 +298,44 @@ int launch_fast_np(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mo
   return hipGetLastError() == hipSuccess ? GCAPS_OK : GCAPS_EDEVICE;
 }
 
-/* Tasksets per wavefront of the screen.  A tile keeps a row of LDS per task: with 80 tasks of 64 tasksets a compute unit holds six
- * wavefronts, with 32 thirteen, whose loads cover each other, and 100,000 tasksets are one round of them instead of one and a
- * little.  Fewer tasks leave room for enough of either, and the wider tile keeps all lanes at work in the walk; a batch of up to 256
- * tasksets per CU has too few wide tiles.  us with 64 / 32, both policies, busy-waiting, overloaded: 80 tasks x 5 segments, 5,000 tasksets 55.7 / 42.3,
- * 100,000 137.8 / 109.3, 200,000 215.2 / 168.6; 80 x 3, 100,000 166.9 / 141.3; 40 x 5, 100,000 87.5 / 95.0, 200,000 140.0 / 130.9;
- * 40 x 3, 65,536 90.2 / 91.9, 400,000 210.0 / 195.6; 32 x 6, 100,000 78.8 / 86.4, 400,000 178.2 / 179.6; 32 x 3, 100,000 89.3 / 84.6,
- * 400,000 182.0 / 168.7; 24 x 3, 33,333 60.9 / 58.8, 100,000 71.0 / 72.7; 20 x 3, 65,536 56.8 / 55.3, 400,000 127.0 / 139.4. */
-u32 screen_width(const gcaps_ctx *ctx, const gcaps_batch *b) {
-  const u32 n = b->n_tasks;
-  return n > 32u || (n > 24u && b->max_gseg <= 4u) || b->n_tasksets <= 256u * (u32)ctx->n_cu ? 32u : 64u;
+/* Tasksets per wavefront of the screen.  Tiles of 32 are quicker one by one (half the rows of LDS, half the elements) and twice as
+ * many.  Up to ten tasks leave a tile of 32 too little to do, and 64 are the better ones.  Of more tasks
+ *  - 32 are, as long as all of them are resident at once: twelve wavefronts per CU by the registers of five to eight segments (151),
+ *    sixteen of up to four, fewer by LDS from 64 tasks on;
+ *  - beyond that 64 up to 24 tasks, which keep all lanes at work in the walk (the line at twelve wavefronts of 32 per CU for up to four
+ *    segments as well);
+ *  - of more tasks 64 where those are resident at once and no more than fifteen wavefronts of 32 would be, else 32 again: neither is, and
+ *    half-filled last rounds cost less in smaller tiles.
+ * us with 64 / 32, both policies, busy-waiting, overloaded (mixed):
+ *   1 x 1, round-robin alone, 46,080 tasksets 19.2 / 27.6, 6 x 1, 81,920 29.2 / 33.1 (mixed), 10 x 3, 61,440 33.8 / 35.6 (lightly loaded);
+ *   12 x 4 and 14 x 5, 46,080 0.93 (0.98) times as long with 32, round-robin alone 0.87;
+ *   20 x 3, 60,000 34.4 / 31.8 (58.5 / 57.1), 95,000 36.9 / 35.0 (64.2 / 65.6), 105,000 37.3 / 35.9 (65.9 / 68.7), 205,000 53.1 / 54.5
+ *   (86.5 / 94.3); 24 x 3, 60,000 33.0 / 29.6 (72.0 / 69.6), 125,000 42.2 / 41.9 (82.2 / 86.4), 400,000 98.7 / 94.7 (143.0 / 149.6);
+ *   24 x 6, 95,000 32.3 / 33.0 (84.0 / 80.3), 105,000 40.6 / 48.3 (85.2 / 95.9), 205,000 70.5 / 68.9 (116.9 / 120.6);
+ *   28 x 3, 60,000 27.4 / 24.7, 165,000 53.8 / 55.3 (106.6 / 110.0), 205,000 70.1 / 61.7 (127.6 / 115.5);
+ *   32 x 3, 125,000 46.3 / 40.9 (106.2 / 99.5), 205,000 83.6 / 66.8 (139.7 / 125.3); 40 x 3, 150,000 55.8 / 53.5 (136.8 / 138.6), 165,000
+ *   74.7 / 58.2 (171.7 / 156.7); 80 x 3, 60,000 53.8 / 44.8, 95,000 69.4 / 80.4 (119.4 / 130.4), 105,000 106.2 / 82.4 (164.7 / 142.3);
+ *   40 x 5, 95,000 42.5 / 38.6 (88.5 / 84.9), 105,000 44.5 / 49.3 (92.9 / 104.2), 165,000 76.2 / 61.1 (130.5 / 117.9); 64 x 5, 95,000
+ *   61.2 / 60.0 (88.3 / 79.2), 105,000 68.9 / 75.9 (94.7 / 104.4), 125,000 101.4 / 81.6; 72 x 5, 105,000 101.6 / 79.3;
+ *   80 x 5, 5,000 38.3 / 28.2 (54.9 / 44.0), 60,000 54.4 / 46.0, 95,000 70.3 / 81.8 (95.7 / 106.8), 105,000 108.2 / 83.1 (140.0 / 110.4), 200,000
+ *   170.2 / 135.1. */
+template <bool BUSY, int SEGS>
+u32 screen_width(const gcaps_ctx *ctx, const gcaps_batch *b, u32 kr) {
+  if (ctx->screen_width) return ctx->screen_width;
+  const u32 n = b->n_tasks, N = b->n_tasksets, cu = (u32)ctx->n_cu;
+  if (n <= 10u) return 64u;
+  if (n <= 24u) return N <= 384u * cu ? 32u : 64u;
+  if (N <= 256u * cu) return 32u;
+  /* wavefronts per CU; LDS is handed out in pieces of 1,280 bytes, which the query does not round up to */
+  auto resident = [&](const void *fn, u32 width) -> u32 {
+    const size_t lds = fast::lds_bytes(n, kr, width, true);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64, lds) != hipSuccess) (void)hipGetLastError();
+    return std::min((u32)per_cu, (u32)(ctx->lds_total / ((lds + 1279u) / 1280u * 1280u)));
+  };
+  const u32 narrow = resident((const void *)fast::rta_screen_kernel<BUSY, SEGS, 32>, 32u);
+  if (narrow >= 16u || (N + 31u) / 32u <= cu * narrow) return 32u;
+  return (N + 63u) / 64u <= cu * resident((const void *)fast::rta_screen_kernel<BUSY, SEGS, 64>, 64u) ? 64u : 32u;
 }
 
 int launch_screen(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, int64_t *d_resp,
@@ -320,8 +349,10 @@ int launch_screen(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mod
                        ctx->resp_stride, ctx->sched_stride, ctx->ts_offset);
   };
   auto with_segs = [&](auto busy, auto segs) {
-    if (screen_width(ctx, b) == 32u) launch(busy, segs, std::integral_constant<int, 32>{});
-    else launch(busy, segs, std::integral_constant<int, 64>{});
+    if (screen_width<decltype(busy)::value, decltype(segs)::value>(ctx, b, kr) == 32u)
+      launch(busy, segs, std::integral_constant<int, 32>{});
+    else
+      launch(busy, segs, std::integral_constant<int, 64>{});
   };
   auto with = [&](auto busy) {
     if (b->max_gseg <= (u32)fast::kCacheSegs) with_segs(busy, std::integral_constant<int, fast::kCacheSegs>{});
@@ -1115,6 +1146,10 @@ extern "C" int gcaps_create(gcaps_ctx **out, int device_id, void *hip_stream) {
   if (const char *e = getenv("GCAPS_SCREEN_TASKS")) {
     const long v = strtol(e, nullptr, 10);
     if (v >= 1 && v <= 255) ctx->screen_tasks = (u32)v;
+  }
+  if (const char *e = getenv("GCAPS_SCREEN_WIDTH")) {
+    const long v = strtol(e, nullptr, 10);
+    if (v == 32 || v == 64) ctx->screen_width = (u32)v;
   }
   if (const char *e = getenv("GCAPS_ONE_LAUNCH")) {
     const long v = strtol(e, nullptr, 10);

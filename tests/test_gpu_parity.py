@@ -618,33 +618,47 @@ def test_continue_after_miss_small_calls(oracle, gpu, cores, per_core, S, N):
     compare_continue(oracle, B, batch, GCAPS, waits=(SUSPEND,))
 
 
-@pytest.mark.parametrize("cores,per_core,S", [(1, 1, 5), (4, 5, 3), (4, 5, 6), (4, 6, 7), (4, 7, 4), (4, 8, 8), (3, 11, 5), (8, 10, 5), (8, 10, 0), (5, 20, 2)])
-@pytest.mark.parametrize("N", [1, 31, 33, 2_017])
-def test_screen_tile_widths(oracle, monkeypatch, cores, per_core, S, N):
-    """The first launch in tiles of 32 tasksets (its smaller batches and its many tasks), up to eight segment slots: ragged last tiles,
-    an invalid taskset, one outside the 24-bit range."""
+@pytest.mark.parametrize("width", ["32", "64"])
+@pytest.mark.parametrize("cores,per_core,S", [(1, 1, 5), (1, 2, 0), (1, 3, 8), (4, 5, 3), (4, 5, 6), (4, 6, 7), (4, 7, 4), (4, 8, 8), (3, 11, 5),
+                                              (8, 10, 5), (8, 10, 0), (5, 20, 2)])
+@pytest.mark.parametrize("N", [1, 31, 33, 65, 2_017])
+def test_screen_tile_widths(oracle, monkeypatch, width, cores, per_core, S, N):
+    """The first launch in tiles of 32 and of 64 tasksets, up to eight segment slots: ragged last tiles, one policy alone, an invalid
+    taskset, one outside the 24-bit range."""
     import torch
     from paper_2406_05221_amd import binding as B
     monkeypatch.setenv("GCAPS_ONE_LAUNCH", "0")
+    monkeypatch.setenv("GCAPS_SCREEN_WIDTH", width)
     ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
     try:
         batch = relaxed_workload(N, seed=N + S, n_cores=cores, per_core=per_core, S=S)
         batch["period_us"][N - 1, 0] = batch["deadline_us"][N - 1, 0] = 2**25
-        for policy in (BOTH, GCAPS):
+        for policy in (BOTH, GCAPS, RR):
             compare(oracle, B, ctx, batch, policy)
-        bad = {k: v.copy() for k, v in batch.items()}
-        bad["period_us"][N // 2, 0] = 0
-        with pytest.raises(B.GcapsError) as e:
-            B.gcaps_rta_batch(ctx, bad, BOTH, SUSPEND)
-        assert e.value.first_bad == N // 2
+        for at in (N // 2, N - 1):
+            bad = {k: v.copy() for k, v in batch.items()}
+            bad["period_us"][at, 0] = 0
+            with pytest.raises(B.GcapsError) as e:
+                B.gcaps_rta_batch(ctx, bad, BOTH, SUSPEND)
+            assert e.value.first_bad == at
     finally:
         B.gcaps_destroy(ctx)
 
 
-@pytest.mark.parametrize("S,N", [(3, 65_536), (3, 65_537), (6, 65_537)])
-def test_screen_width_at_its_line(oracle, gpu, S, N):
+@pytest.mark.parametrize("cores,per_core,S,N", [
+    (2, 5, 3, 70_001), (1, 11, 3, 70_001), (4, 5, 3, 98_304), (4, 5, 3, 98_305), (4, 7, 6, 98_305), (5, 8, 3, 98_305), (5, 8, 5, 98_305),
+    (8, 10, 5, 90_112), (8, 10, 5, 90_113), (8, 10, 3, 98_305)])
+def test_screen_width_at_its_lines(oracle, gpu, cores, per_core, S, N):
+    """Shapes and sizes of the first launch that take 32 or 64 tasksets per wavefront by default (256 compute units: lines at 98,304
+    tasksets, at 90,112 of 80 tasks; 64 up to ten tasks).  Many tasks: overloaded, so that the oracle is done in time."""
+    from paper_2406_05221_amd import taskgen
     B, ctx, _ = gpu
-    compare(oracle, B, ctx, relaxed_workload(N, seed=S, n_cores=4, per_core=5, S=S))
+    if cores * per_core <= 28:
+        batch = relaxed_workload(N, seed=S, n_cores=cores, per_core=per_core, S=S)
+    else:
+        batch = taskgen.generate(N, n_cores=cores, tasks_per_core=per_core, max_gseg=S, util=(0.3, 0.9), eta=(0, S),
+                                 share=(0.10, 0.60), period=(1_000, 1_000_000), overhead=(50, 500), slice_us=1024, seed=S, stream=81)
+    compare(oracle, B, ctx, batch, waits=(SUSPEND,))
 
 
 def test_continue_after_miss_mixed_cases(oracle, gpu):
