@@ -315,8 +315,10 @@ int gcaps_gprio_rta_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, int w
  * A recorded call uses no scratch that another call could grow: it needs no direct call before it, and its graph stays
  * valid whatever the context does afterwards.  (A direct call hands the tasksets out longest schedule first, from a
  * list of 12 bytes per taskset that the context keeps; a recorded one in caller order.)
- * One lane simulates one taskset under one policy and jumps from event to event (end of a segment, slice,
- * switch or update; a release).  gcaps_simulate_batch takes HOST pointers and returns when the results are in
+ * One lane simulates one taskset under one policy and jumps from event to event (end of a stretch on the CPU, which is a
+ * CPU segment and the launch part behind it, of GPU work, a slice, a switch or an update; a release).  While a schedule
+ * runs, its lane keeps words of its own in out_mort and out_jobs and reads them back: device memory is the place for them.
+ * gcaps_simulate_batch takes HOST pointers and returns when the results are in
  * place; gcaps_simulate_batch_device takes DEVICE pointers, queues the work on the context's stream and
  * returns (errors as gcaps_rta_batch_device; gcaps_status reports on it likewise).
  */
@@ -401,8 +403,9 @@ int gcaps_table3_generate_device(gcaps_ctx *ctx, const gcaps_table3_spec *spec, 
 
 /*
  * Diagnostics of the most recent gcaps_simulate_batch[_device] call (waits for the stream): the number of
- * steps its lanes took in total, a step being one jump to the next event of a taskset's schedule (Sec. 6.2
- * defines no such count; it measures the work of the simulation).
+ * steps its lanes took in total, a step being one jump to the next event of a taskset's schedule, see
+ * gcaps_simulate_batch (Sec. 6.2 defines no such count; it measures the work of the simulation.  What is one event may
+ * change with the library: counts of different versions are not comparable).
  */
 int gcaps_last_sim_steps(gcaps_ctx *ctx, uint64_t *steps);
 
