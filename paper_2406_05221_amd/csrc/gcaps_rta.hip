@@ -984,11 +984,10 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
   });
 }
 
-/* The longest schedules first; null (caller order) where there is no memory for the list, for a few tasks (schedules
- * short enough for the sort and the scattered reads behind it to show: 65,536 tasksets of 6 tasks, a horizon of 200,000,
- * 2.49 ms in caller order, 2.72 by length, with the kernel's first form), or where the stream is recording: a recorded
- * simulation uses nothing but the status block, which stays where it is as long as the context lives, so that it can be
- * replayed whatever calls grow the context's buffers afterwards. */
+/* The longest schedules first; null (caller order) where there is no memory for the list, for a few tasks (the figures stand
+ * at sim::kShortPhases), or where the stream is recording: a recorded simulation uses nothing but the status block, which
+ * stays where it is as long as the context lives, so that it can be replayed whatever calls grow the context's buffers
+ * afterwards. */
 const u32 *simulation_order(gcaps_ctx *ctx, const gcaps_batch *sub, u32 horizon) {
   const u32 N = sub->n_tasksets, blocks = (N + 255u) / 256u;
   if (sub->n_tasks <= sim::kFewTasks || ctx->capturing) return nullptr;
