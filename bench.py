@@ -56,8 +56,8 @@ MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="111b11f94673dfabe26b0e2d45553365b660b
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged
 RTA_SOURCES = ("gcaps_rta.hip", "rta_fast.hip.inc", "rta_quad.hip.inc", "rta_deep.hip.inc", "rta_wide.hip.inc",
                "rta_bin.hip.inc")
-GPRIO_SOURCES = ("gcaps_rta.hip", "rta_fast.hip.inc", "rta_wide.hip.inc", "gprio_tile.hip.inc", "gprio_fast.hip.inc",
-                 "gprio_wide.hip.inc")
+GPRIO_SOURCES = ("gcaps_rta.hip", "rta_fast.hip.inc", "rta_wide.hip.inc", "rta_deep.hip.inc", "gprio_tile.hip.inc",
+                 "gprio_fast.hip.inc", "gprio_wide.hip.inc")
 
 
 def csrc_sha256(names=RTA_SOURCES):

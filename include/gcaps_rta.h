@@ -140,7 +140,7 @@ enum {
  *   GCAPS_GEN_KERNEL      "taskset": gcaps_taskgen_device with one lane per taskset (default: one lane per task)
  *   GCAPS_GPRIO_KERNEL    "list": the priority search as two launches, the second packing sixteen searched
  *                         tasksets per wavefront (faster when most tasksets are searched deeply; default: one
- *                         pass in which a wavefront reads, searches and answers 16 consecutive tasksets)
+ *                         pass in which a wavefront reads, searches and answers 4 to 16 consecutive tasksets)
  */
 int gcaps_create(gcaps_ctx **out, int device_id, void *hip_stream);
 
@@ -181,6 +181,9 @@ int gcaps_rta_batch(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wa
  * replayed any number of times, with direct calls in between.  The same holds for the other device-resident entry points
  * (gcaps_gprio_assign_batch_device, gcaps_gprio_rta_batch_device); recorded simulations use no such scratch, see
  * gcaps_simulate_batch.
+ * A small call redoes tasksets outside the 24-bit range in its one launch where the context holds 64-bit columns for all
+ * of its tasksets, else in a launch behind it, for which the columns are allocated: the first call of a context, and a later
+ * one of more tasksets times tasks than any before it, takes a launch and an allocation more.
  */
 int gcaps_rta_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, int policy, int wait_mode,
                            int64_t *d_out_resp, uint8_t *d_out_sched);
@@ -267,7 +270,7 @@ int gcaps_gprio_assign_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, in
  *              it is reported like a task-model violation (GCAPS_ETASK, smallest index)
  *   out_resp   int64 [n_tasksets][n_tasks]: R_i, or GCAPS_RESP_MISS where the bound exceeds D_i
  *   out_sched  uint8 [n_tasksets]: 1 iff no task missed
- * Up to 32 tasks per taskset run in a quad-lane 24-bit kernel (tasksets whose numbers leave its range are
+ * Up to 32 tasks per taskset run in a 24-bit kernel of 4 to 16 lanes per taskset (tasksets whose numbers leave its range are
  * handed to the general 64-bit kernel, as gcaps_last_wide_count reports); results are exact on both routes.
  * Host / device variants and error reporting as for gcaps_gprio_assign_batch[_device].
  */
@@ -313,8 +316,9 @@ int gcaps_gprio_rta_batch_device(gcaps_ctx *ctx, const gcaps_batch *batch, int w
  * Limits: n_tasks <= 32 (else GCAPS_EINVAL); a taskset with T = 0, L = 0, eta^g > S or a core index >= 64
  * makes the call fail with GCAPS_ETASK (smallest index; outputs unspecified).
  * A recorded call uses no scratch that another call could grow: it needs no direct call before it, and its graph stays
- * valid whatever the context does afterwards.  (A direct call hands the tasksets out longest schedule first, from a
- * list of 12 bytes per taskset that the context keeps; a recorded one in caller order.)
+ * valid whatever the context does afterwards.  (A direct call of more than eight tasks keeps a
+ * list of 12 bytes per taskset and hands the tasksets out longest schedule first unless all are short; others, and a recorded one, in caller
+ * order.)
  * One lane simulates one taskset under one policy and jumps from event to event (end of a stretch on the CPU, which is a
  * CPU segment and the launch part behind it, of GPU work, a slice, a switch or an update; a release).  While a schedule
  * runs, its lane keeps words of its own in out_mort and out_jobs and reads them back: device memory is the place for them.
