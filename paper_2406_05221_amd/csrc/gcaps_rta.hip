@@ -524,23 +524,16 @@ u32 given_lanes(const gcaps_ctx *ctx, u32 n, u32 N) {
   return n > 20 || N <= (n <= 8 ? 64u : 96u) * cu ? 8u : 4u;
 }
 
-/* Tasksets per CU up to which a kernel redoes in 64 bit, where it finds them, the tasksets outside the 24-bit range; a larger call lists
- * them for a launch of full wavefronts behind it.  Four to sixteen lanes of a wavefront work then, so that a call all of whose
- * tasksets are outside soon takes longer; one with none saves the empty launch, 2.2 us.  us with a list / where they are found, all outside
- * (periods of 3 to 30 seconds; light loads, then overloaded ones):
- *   analysis: 6 tasks, 1,000 tasksets 162 / 95, 40,960 192 / 185, 49,152 205 / 283; 24 tasks, 9,216 3,308 / 2,469, 40,960 2,864 / 2,785,
- *   49,152 2,928 / 4,498;
- *   search: 16, 4,096 8,139 / 2,183, 16,384 8,462 / 4,065 and 447 / 402, 24,576 8,496 / 3,851 and 472 / 518; 24, 16,384 831 / 805, 24,576
- *   854 / 1,016; 6, 49,152 518 / 587;
- *   given: 16, 4,096 1,386 / 1,012, 16,384 1,338 / 1,366; 24, 16,384 3,250 / 3,277, 20,480 3,262 / 4,157; 32, 12,288 6,470 / 6,446, 16,384
- *   6,113 / 7,554. */
-constexpr u32 kRedoAnalysis = 160u, kRedoSearch = 64u;
-u32 redo_given(u32 n) { return n > 24u ? 48u : 64u; }
-
-/* columns of the 64-bit kernels for every taskset of a call, if they are there already */
-bool columns_at_hand(gcaps_ctx *ctx, u32 n, u32 N, u32 most_per_cu, wide::Scratch *ws) {
+/* Columns of the 64-bit kernels for every taskset of a call, if they are there already: what is outside the 24-bit range is redone
+ * where it is found, and the launch over a list behind, 2.2 us when there is nothing to do, falls away.  The search and the analysis of
+ * given priorities put all lanes of a taskset to this (figures at search_wide).  The analysis one: us with a list / where they are found,
+ * periods of 3 to 30 seconds in one taskset of fifty (in all): 6 tasks, 1,000 tasksets 84 / 55 (107 / 75), 40,960 128 / 96 (142 / 154), 49,152
+ * 134 / 105 (153 / 164); 24 tasks, 9,216 1,246 / 658 (1,406 / 1,591), 49,152 1,408 / 1,090 (1,539 / 2,942).  With all lanes at it those of one in
+ * fifty take 37, 68, 72, and a half to a tenth for all, but the walk then has too few scalar registers: calls of 8,000 to 13,000 tasksets
+ * without one outside 2 to 4 % longer (20 tasks x 4 segments 19.6 -> 20.4). */
+bool columns_at_hand(gcaps_ctx *ctx, u32 n, u32 N, wide::Scratch *ws) {
   const u32 slots = wide_slots(ctx, N);
-  return N <= most_per_cu * (u32)ctx->n_cu && slots >= N && ctx->pool.wide_scratch.bytes >= wide_column_bytes(n, slots) && wide_columns(ctx, n, slots, ws) == GCAPS_OK;
+  return slots >= N && ctx->pool.wide_scratch.bytes >= wide_column_bytes(n, slots) && wide_columns(ctx, n, slots, ws) == GCAPS_OK;
 }
 
 bool quad_all_applies(const gcaps_ctx *ctx, const gcaps_batch *b) {
@@ -650,7 +643,7 @@ int run_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int policy, int wait_mode, i
   if (ctx->wide_only) return launch_wide(ctx, b, policy, wait_mode, d_resp, d_sched, nullptr, nullptr, N);
   const bool one = ctx->cont ? continue_small(ctx, b) : one_launch_applies(ctx, b, policy);
   wide::Scratch ws{};
-  if (one && n <= kSmallTasks && columns_at_hand(ctx, n, N, kRedoAnalysis, &ws)) {
+  if (one && n <= kSmallTasks && columns_at_hand(ctx, n, N, &ws)) {
     /* With a column for every taskset what is outside the fast range is redone where it is found.  Columns that are not there yet
      * are allocated by a launch over a list behind this one, while this one runs (a context's first call of 9,000 tasksets of 16
      * tasks: 45 us, 54 with the allocation in front of the only launch). */
@@ -824,7 +817,7 @@ int run_gprio_chunk(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const u
      * writes their outputs */
     const u32 lanes = search_lanes(ctx, n, N);
     wide::Scratch own{};
-    const bool alone = lanes > 4u && columns_at_hand(ctx, n, N, kRedoSearch, &own);
+    const bool alone = lanes > 4u && columns_at_hand(ctx, n, N, &own);
     int rc = alone ? GCAPS_OK : ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
     if (rc != GCAPS_OK) return rc;
     u32 *wl = (u32 *)ctx->pool.wide_list.ptr;
@@ -935,7 +928,7 @@ int run_gprio_given(gcaps_ctx *ctx, const gcaps_batch *b, int wait_mode, const i
     if (!ctx->wide_only) {
       const u32 lanes = given_lanes(ctx, nt, N);
       wide::Scratch own{};
-      const bool alone = lanes > 4u && columns_at_hand(ctx, nt, N, redo_given(nt), &own);
+      const bool alone = lanes > 4u && columns_at_hand(ctx, nt, N, &own);
       int rc = alone ? GCAPS_OK : ctx->pool.wide_list.reserve((size_t)N * sizeof(u32), !ctx->capturing);
       if (rc != GCAPS_OK) return rc;
       u32 *wl = (u32 *)ctx->pool.wide_list.ptr;

@@ -847,30 +847,49 @@ def test_recorded_call_after_a_direct_one_on_another_route(oracle, gpu, per_cu, 
         B.gcaps_destroy(ctx)
 
 
-@pytest.mark.parametrize("call,per_core,per_cu", [("rta", 1, 160), ("search", 2, 64), ("given", 3, 64), ("given", 7, 48)])
-@pytest.mark.parametrize("beyond", [0, 1])
-def test_calls_outside_the_24_bit_range(oracle, gpu, call, per_core, per_cu, beyond):
-    """At most so many tasksets per CU are redone in 64 bit where they are found, more of them by a launch over a list: every
-    taskset is outside the range, all of them twice (the first call of a context has a list in any case)."""
+@pytest.mark.parametrize("call,per_core,per_cu", [
+    ("rta", 1, 160), ("rta", 6, 6), ("rta", 3, 30), ("rta", 6, 60), ("continue", 5, 10), ("continue", 3, 50),
+    ("search", 2, 64), ("search", 5, 6), ("search", 7, 30), ("given", 3, 64), ("given", 7, 48), ("given", 5, 6)])
+@pytest.mark.parametrize("every", [1, 3])
+def test_calls_outside_the_24_bit_range(oracle, gpu, call, per_core, per_cu, every):
+    """Small calls redo in 64 bit where they find it what is outside the range, the search and the analysis of given priorities with all
+    eight or sixteen lanes of a taskset: every taskset is outside, or every third, in calls of each number of lanes, all of them twice
+    (the first call of a context has a list in any case).  One that the redo finds invalid is reported."""
     import torch
     B, _, _ = gpu
-    N = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + beyond
+    N = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + 1
     batch = relaxed_workload(N, seed=per_core, per_core=per_core, S=1)
     for key in ("cpu_us", "period_us", "deadline_us", "gm_us", "ge_us"):
-        batch[key] = np.minimum(batch[key].astype(np.uint64) * 300, 2**32 - 1).astype(np.uint32)
+        far = np.minimum(batch[key][::every].astype(np.uint64) * 300, 2**32 - 1)
+        batch[key][::every] = far.astype(np.uint32)
     ctx = B.gcaps_create(0, torch.cuda.Stream().cuda_stream)
     try:
+        if call == "continue":
+            B.gcaps_set_continue_after_miss(ctx, True)
         for _ in range(2):
             if call == "rta":
-                compare(oracle, B, ctx, batch, waits=(SUSPEND,))
+                compare(oracle, B, ctx, batch, waits=(SUSPEND, BUSY))
+            elif call == "continue":
+                for wait in (SUSPEND, BUSY):
+                    got = B.gcaps_rta_batch(ctx, batch, BOTH, wait)
+                    want = oracle.rta_batch(batch, BOTH, wait, threads=16, options=oracle.OPT_CONTINUE_AFTER_MISS)
+                    assert all(np.array_equal(x, y) for x, y in zip(got, want[:2]))
             elif call == "search":
-                got = B.gcaps_gprio_assign_batch(ctx, batch, BUSY)
-                assert all(np.array_equal(x, y) for x, y in zip(got, oracle.gprio_assign_batch(batch, BUSY, threads=16)[:3]))
+                for wait in (SUSPEND, BUSY):
+                    got = B.gcaps_gprio_assign_batch(ctx, batch, wait)
+                    assert all(np.array_equal(x, y) for x, y in zip(got, oracle.gprio_assign_batch(batch, wait, threads=16)[:3]))
             else:
-                got = B.gcaps_gprio_rta_batch(ctx, batch, SUSPEND, batch["prio"])
-                want = oracle.gprio_rta_batch(batch, batch["prio"], SUSPEND)
-                assert all(np.array_equal(x, y) for x, y in zip(got, want))
-            assert B.gcaps_last_wide_count(ctx) == N
+                for wait in (SUSPEND, BUSY):
+                    got = B.gcaps_gprio_rta_batch(ctx, batch, wait, batch["prio"])
+                    want = oracle.gprio_rta_batch(batch, batch["prio"], wait)
+                    assert all(np.array_equal(x, y) for x, y in zip(got, want))
+            assert B.gcaps_last_wide_count(ctx) >= len(range(0, N, every))
+        if call == "given":
+            bad = batch["prio"].copy()
+            bad[[every * 7, every * 40]] *= -1  # the two orders disagree on every core
+            with pytest.raises(B.GcapsError) as e:
+                B.gcaps_gprio_rta_batch(ctx, batch, BUSY, bad)
+            assert e.value.first_bad == every * 7
     finally:
         B.gcaps_destroy(ctx)
 
