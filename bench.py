@@ -33,24 +33,24 @@ OPS_PER_TERM = 6                           # add jitter, reciprocal ceil-div (~3
 # instruction), per workload and waiting mode, 1,000,000 tasksets; valid for the kernel sources they were
 # taken with (profiles/rta_step_workload3_counters.md, profiles/rta_step_workload0_counters.md).
 MEASURED_VALU = dict(
-    csrc_sha256="9b0785c53ab94305096a0c562506b6d1d1258bee501ebc843addd4e79e23aeb0", tasksets=1_000_000,
-    per_workload={"3": dict(busy=dict(valu_wave_insts=56_962_893, valu_lane_ops=2_598_784_221),
-                            suspend=dict(valu_wave_insts=61_959_281, valu_lane_ops=2_699_261_689)),
-                  "0": dict(busy=dict(valu_wave_insts=355_112_752, valu_lane_ops=20_370_862_350),
-                            suspend=dict(valu_wave_insts=529_792_558, valu_lane_ops=30_351_477_073))})
+    csrc_sha256="09743d398ce775249acd2c2fee3a5f02420ecee39e68fc0737f7b99f51578328", tasksets=1_000_000,
+    per_workload={"3": dict(busy=dict(valu_wave_insts=56_965_954, valu_lane_ops=2_598_969_940),
+                            suspend=dict(valu_wave_insts=61_942_321, valu_lane_ops=2_698_260_482)),
+                  "0": dict(busy=dict(valu_wave_insts=355_111_847, valu_lane_ops=20_370_807_807),
+                            suspend=dict(valu_wave_insts=529_779_278, valu_lane_ops=30_350_705_803))})
 
 # HBM bytes of one default step (workload 3, both policies; mean of the two waiting modes), from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE summed over the launches of a step and scaled by what the same
 # counters read for a device-to-device copy of 1 GiB (profiles/rta_step_workload3_hbm_traffic.md).
 # Valid only for the kernel sources the counters were taken with (RTA_SOURCES / GPRIO_SOURCES below).
-MEASURED_TRAFFIC = dict(csrc_sha256="9b0785c53ab94305096a0c562506b6d1d1258bee501ebc843addd4e79e23aeb0",
-                        workload=3, tasksets=1_000_000, fetch_bytes=915859547, write_bytes=328828251)
+MEASURED_TRAFFIC = dict(csrc_sha256="09743d398ce775249acd2c2fee3a5f02420ecee39e68fc0737f7b99f51578328",
+                        workload=3, tasksets=1_000_000, fetch_bytes=915636429, write_bytes=328834816)
 
 
 # The same for `--row gprio` (workload 3; the skip flags of the run; mean of the two waiting modes;
 # profiles/gprio_step_workload3_hbm_traffic.md).
-MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="111b11f94673dfabe26b0e2d45553365b660b6969398d0b52b61066ea9b64b17",
-                              workload=3, tasksets=1_000_000, fetch_bytes=877797970, write_bytes=242013691)
+MEASURED_TRAFFIC_GPRIO = dict(csrc_sha256="25c1e8584ab130ab92b2a725183a8cb98a16b1aadef5085b9b5ac89fe7ffc140",
+                              workload=3, tasksets=1_000_000, fetch_bytes=877588582, write_bytes=242012211)
 
 
 # the sources a row's kernels are built from: its counters stay valid while these are unchanged
